@@ -153,7 +153,7 @@ def serving_leg(nep, synth, params_of, n_req, budget_gb, prec):
         return srv.submit(r.pos, r.types, r.box, kind=nep.NEP_REQ_MD, vel=r.vel,
                           masses=masses, n_steps=r.n_steps, dt=1.0)
 
-    # warm-up (autotuner, workspace growth) on a few requests
+    # warm-up (workspace growth) on a few requests
     for r in reqs[:4]:
         srv.poll(submit(r), wait_ms=-1)
     srv.reset_stats()
@@ -197,7 +197,7 @@ def batch_leg(nep, synth, torch, n_struct, n_sets, reps=3):
     8-256 atoms, 3 species, evaluated (energy, forces, virial) for n_sets
     parameter vectors z_p = mean + 0.1 eps_p in one nep_compute_batch call
     (rows built once and shared; the per-set passes replayed as one HIP
-    graph).  The first call fixes the kernel shapes (autotuner); the next
+    graph).  The first call grows the workspace; the next
     `reps` calls are timed whole (rows, graph capture and launch included);
     one more call with HIP-event stage timing gives the graph launch alone."""
     dev = torch.device("cuda:0")
@@ -426,7 +426,8 @@ def main():
     dt, stages, th = results[nep.NEP_MLP_FP32]
     value = n * args.steps / dt
     fl = algorithmic_flops(h, p_r, p_a)
-    force_kernel = f"k_partial_forces<{tune['ng_force']}, {h['l_max_3b']}, false, {tune['lanes_force']}>"
+    # template arguments: tiles of four radial functions, l_max, batch, quads of lanes per atom
+    force_kernel = f"k_partial_forces<{(tune['ng_force'] + 3) // 4}, {h['l_max_3b']}, false, {tune['lanes_force']}>"
     tr = measured_traffic(force_kernel)
     avg = {k: v[0] / v[1] for k, v in stages.items()}
     dom = max(("descriptor", "partial_forces"), key=lambda k: avg.get(k, 0.0))

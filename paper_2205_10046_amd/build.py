@@ -22,7 +22,7 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
-SOURCES = ["api.cpp", "neighbor.hip", "descriptor.hip", "mlp.hip", "output.hip",
+SOURCES = ["descriptor.hip", "force.hip", "api.cpp", "neighbor.hip", "mlp.hip", "output.hip",
            "md.hip", "ensemble.hip", "params.hip"]
 
 

@@ -15,6 +15,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "nep_internal.h"
 
 namespace nep {
@@ -132,6 +134,55 @@ template <int L, class Fn>
 __device__ __forceinline__ void angular_values(float x, float y, float z, Fn&& fn) {
   angular_terms<L>(x, y, z, [&](int k, float b, float, float, float)
                                 __attribute__((always_inline)) { fn(k, b); });
+}
+
+// f(integral_constant<int, J>) for J = A .. B - 1.
+template <int A, int B, class Fn>
+__device__ __forceinline__ void static_for(Fn&& f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    static_for<A + 1, B>(f);
+  }
+}
+
+// The force pass takes the polynomials ordered by m, then cos before sin,
+// then l, and scaled to monic ones: b_k = scale Q_{l,m}(z) {C_m, S_m} with
+// Q_{l,m} the monic multiple of P_l^{(m)}, of degree l - m, and C_m + i S_m =
+// (x + i y)^m.  Then d Q_{l,m} / dz = (l - m) Q_{l,m+1}, so one table of
+// Q gives the sums and their z derivatives, and the terms of one m meet in
+// two numbers (the sums over l) before they touch x and y.
+struct Harmonic {
+  int l, m, sine, k;   // k: the index of b_k
+  double scale;
+};
+
+// Entry `slot` of that order for l <= L.
+constexpr Harmonic harmonic_at(int slot, int L) {
+  constexpr double alpha[5][5] = {{0, 0, 0, 0, 0},
+                                  {1.0, 1.0, 0, 0, 0},
+                                  {2.0, 1.0 / 3.0, 1.0 / 3.0, 0, 0},
+                                  {2.0, 2.0 / 3.0, 1.0 / 15.0, 1.0 / 15.0, 0},
+                                  {8.0, 2.0 / 5.0, 2.0 / 15.0, 1.0 / 105.0, 1.0 / 105.0}};
+  for (int m = 0; m <= L; ++m)
+    for (int sine = 0; sine <= (m > 0 ? 1 : 0); ++sine)
+      for (int l = m > 1 ? m : 1; l <= L; ++l)
+        if (slot-- == 0) {
+          const int k = l * l - 1 + (m ? 2 * m - 1 + sine : 0);
+          const double lead = legendre_dm(l, m).c[l - m];
+          return Harmonic{l, m, sine, k, lead * (l <= 4 ? alpha[l][m] : 1.0)};
+        }
+  return Harmonic{0, 0, 0, 0, 0.0};
+}
+
+// Q_{l,m}(z), m <= l, from the powers of z (zz = z^2).
+template <int l, int m>
+__device__ __forceinline__ float monic(float z, float zz) {
+  constexpr int d = l - m;
+  constexpr Poly8 p = legendre_dm(l, m);
+  float v = 1.f;
+#pragma unroll
+  for (int t = d - 2; t >= 0; t -= 2) v = v * zz + (float)(p.c[t] / p.c[d]);
+  return d % 2 ? v * z : v;
 }
 
 }  // namespace nep

@@ -151,6 +151,23 @@ void angular_constants(int L, double* C3, double* C4, double* C5) {
   C5[2] = 21 / (80 * kPi * kPi);
 }
 
+// Whether a model is accepted: its radial table, its angular table in groups
+// of two, four, five or seven functions (as far as n_A and l_max admit them)
+// and T K_R slots for each of 256 lanes within 64 KB.  The kernels' own LDS
+// (pair.h: the same radial table, the groups-of-four angular table or one of
+// the same stride, K_R + 1 slots for 64 atoms) is never more.
+bool tables_fit(const DevModel& M) {
+  const int cap = M.L <= 4 ? 7 : (M.L == 5 ? 5 : 4);
+  int angular = 0;
+  for (int ng : {2, 4, 5, 7}) {
+    if (ng > cap || (ng > M.nA && ng != 2)) continue;
+    const int width = ng == 2 ? 2 : round4(ng);
+    angular = std::max(angular, M.T * M.T * pair_stride((M.nA + ng - 1) / ng * M.KA * width));
+  }
+  const size_t floats = (size_t)round4(M.T * M.T * M.nR * M.KR) + round4(angular) + (size_t)M.T * M.KR * kBlock;
+  return floats * sizeof(float) <= 64 * 1024;
+}
+
 uint16_t to_bf16(float f) {
   uint32_t u;
   std::memcpy(&u, &f, 4);
@@ -281,20 +298,19 @@ struct StageTimes {
 // Device tables of one parameter vector (float32 / bf16 copies).
 struct ModelTables {
   DevModel M{};
-  float *cR = nullptr, *cA = nullptr, *w0 = nullptr, *w0t = nullptr, *b0 = nullptr, *w1 = nullptr;
+  float *cR = nullptr, *cA = nullptr, *cS = nullptr, *w0 = nullptr, *w0t = nullptr, *b0 = nullptr, *w1 = nullptr;
   uint16_t *w0b = nullptr, *w0tb = nullptr;
   void release() {
-    dev_free(cR); dev_free(cA); dev_free(w0); dev_free(w0t); dev_free(b0); dev_free(w1);
+    dev_free(cR); dev_free(cA); dev_free(cS); dev_free(w0); dev_free(w0t); dev_free(b0); dev_free(w1);
     dev_free(w0b); dev_free(w0tb);
   }
 };
 
-// Kernel shape picked for one problem shape (see autotune()).
+// Kernel shape of one kind of call (single structure, batch), see pick_shape().
 struct Tuning {
   bool done = false;
-  int NG_desc = 0, NG_force = 0, block_desc = 256, block_force = 256;
-  int lanes_desc = 1, lanes_force = 1;   // lanes per atom of the pair kernels
-  int lanes_gather = 1;                  // lanes per atom of the force gather
+  int quads = 1;          // quads of lanes per atom of the pair kernels
+  int lanes_gather = 4;   // lanes per atom of the force gather
 };
 
 }  // namespace
@@ -360,6 +376,7 @@ struct nep_handle {
   double* ref_save = nullptr;
   float *q = nullptr, *fp = nullptr, *U = nullptr, *sums = nullptr;
   float4* P = nullptr;
+  float4* disp = nullptr;          // displacements of the exact entries (batches)
   float *F = nullptr, *W = nullptr, *F_save = nullptr;
   double *pos_save = nullptr, *vel_save = nullptr;
   int32_t *types_save = nullptr, *ext_save = nullptr;
@@ -464,6 +481,7 @@ struct nep_handle {
     dev_free(L.nnR); dev_free(L.nlR); dev_free(L.cdR); dev_free(L.revR);
     dev_free(L.nnA);
     dev_free(P);
+    dev_free(disp);
   }
 
   // ---- timing helpers ----
@@ -542,31 +560,29 @@ void upload_model(nep_handle* h, const double* p, ModelTables& mt) {
   }
   const float b1 = (float)p[off++];
   b0[(size_t)nets * NNp] = b1;  // b1 rides at the end of the b0 table
-  std::vector<float> cR((size_t)T * T * nR * KR);
-  for (size_t k = 0; k < cR.size(); ++k) cR[k] = (float)p[off + k];
-  off += cR.size();
-  // one angular table per admissible group size NG: [T][T][groups][KA][ng_pad(NG)]
-  std::vector<float> cA;
-  int32_t cA_off[8];
-  int32_t cA_max = 0;
-  for (int ng = 0; ng < 8; ++ng) cA_off[ng] = -1;
-  int32_t cA_pair[8];
-  for (int ng = 0; ng < 8; ++ng) cA_pair[ng] = 0;
-  for (int ng : angular_group_options(nA, hp.l_max_3b)) {
-    const int groups = (nA + ng - 1) / ng, w = ng_pad(ng);
-    const int ps = pair_stride(groups * KA * w);
-    const size_t base = cA.size();
-    cA_off[ng] = (int32_t)base;
-    cA_pair[ng] = ps;
-    cA.resize(base + (size_t)T * T * ps, 0.f);
-    for (int a = 0; a < T * T; ++a)
-      for (int n = 0; n < nA; ++n)
-        for (int k = 0; k < KA; ++k)
-          cA[base + (size_t)a * ps + ((size_t)(n / ng) * KA + k) * w + n % ng] =
-              (float)p[off + ((size_t)a * nA + n) * KA + k];
-    cA_max = std::max(cA_max, (int32_t)(cA.size() - base));
-  }
+  // the radial table: [T][T][KR][n_R rounded up to 4]
+  const int wR = round4(nR);
+  std::vector<float> cR((size_t)T * T * KR * wR, 0.f);
+  for (int a = 0; a < T * T; ++a)
+    for (int n = 0; n < nR; ++n)
+      for (int k = 0; k < KR; ++k) cR[((size_t)a * KR + k) * wR + n] = (float)p[off + ((size_t)a * nR + n) * KR + k];
+  off += (size_t)T * T * nR * KR;
+  // the angular table: [T][T][KA][n_A rounded up to 4]
+  const int wA = round4(nA), ps = pair_stride(KA * wA);
+  std::vector<float> cA((size_t)T * T * ps, 0.f);
+  for (int a = 0; a < T * T; ++a)
+    for (int n = 0; n < nA; ++n)
+      for (int k = 0; k < KA; ++k) cA[(size_t)a * ps + (size_t)k * wA + n] = (float)p[off + ((size_t)a * nA + n) * KA + k];
   off += (size_t)T * T * nA * KA;
+  // its Chebyshev series (the force pass): halves summed from the highest k down
+  std::vector<float> cS(cA.size(), 0.f);
+  for (int a = 0; a < T * T; ++a)
+    for (int n = 0; n < nA; ++n) {
+      const size_t o = (size_t)a * ps + n;
+      float sum = 0.f;
+      for (int k = KA - 1; k > 0; --k) sum += cS[o + (size_t)k * wA] = 0.5f * cA[o + (size_t)k * wA];
+      cS[o] = cA[o] + sum;
+    }
 
   auto put = [](auto*& dst, const auto& v) {
     using E = std::remove_reference_t<decltype(*dst)>;
@@ -574,19 +590,15 @@ void upload_model(nep_handle* h, const double* p, ModelTables& mt) {
     HIPCHK(hipMemcpy(dst, v.data(), v.size() * sizeof(E), hipMemcpyHostToDevice));
   };
   put(mt.w0, w0); put(mt.w0t, w0t); put(mt.b0, b0); put(mt.w1, w1);
-  put(mt.w0b, w0b); put(mt.w0tb, w0tb); put(mt.cR, cR); put(mt.cA, cA);
+  put(mt.w0b, w0b); put(mt.w0tb, w0tb); put(mt.cR, cR); put(mt.cA, cA); put(mt.cS, cS);
 
   DevModel& M = mt.M;
   M.T = T; M.nR = nR; M.KR = KR; M.nA = nA; M.KA = KA; M.L = hp.l_max_3b;
   M.NB = (hp.l_max_3b + 1) * (hp.l_max_3b + 1) - 1;
   M.ND = nd; M.NDp = (nd + 7) / 8 * 8; M.NN = NN; M.nets = nets;
-  M.has4b = hp.l_max_4b >= 2; M.has5b = hp.l_max_5b >= 1; M.cA_max = cA_max;
-  for (int ng = 0; ng < 8; ++ng) {
-    M.cA_off[ng] = cA_off[ng];
-    M.cA_pair[ng] = cA_pair[ng];
-  }
+  M.has4b = hp.l_max_4b >= 2; M.has5b = hp.l_max_5b >= 1; M.cA_pair = ps;
   M.rcR = (float)hp.rc_radial; M.rcA = (float)hp.rc_angular; M.b1 = mt.b0 + (size_t)nets * NNp;
-  M.cR = mt.cR; M.cA = mt.cA; M.NNp = NNp; M.NDp32 = NDp32;
+  M.cR = mt.cR; M.cA = mt.cA; M.cS = mt.cS; M.NNp = NNp; M.NDp32 = NDp32;
   M.w0 = mt.w0; M.w0t = mt.w0t; M.b0 = mt.b0; M.w1 = mt.w1; M.w0b = mt.w0b; M.w0tb = mt.w0tb;
   double C3[kMaxNB] = {0}, C4[5], C5[3];
   angular_constants(hp.l_max_3b, C3, C4, C5);
@@ -612,17 +624,8 @@ TableLayout table_layout(const nep_hparams& hp, int nd) {
   L.off_b1 = (int64_t)L.nets * (nd + 2) * L.NN;
   L.off_cR = L.off_b1 + 1;
   L.off_cA = L.off_cR + (int64_t)L.T * L.T * L.nR * L.KR;
-  L.n_ng = 0;
-  int64_t cA = 0;
-  for (int ng : angular_group_options(L.nA, hp.l_max_3b)) {
-    const int ps = pair_stride((L.nA + ng - 1) / ng * L.KA * ng_pad(ng));
-    L.ng_of[L.n_ng] = ng;
-    L.cA_pair_of[L.n_ng] = ps;
-    L.cA_off_of[L.n_ng] = cA;
-    cA += (int64_t)L.T * L.T * ps;
-    ++L.n_ng;
-  }
-  L.n_cA = cA;
+  L.cA_pair = pair_stride(L.KA * round4(L.nA));
+  L.n_cA = (int64_t)L.T * L.T * L.cA_pair;
   auto take = [](int64_t& at, int64_t bytes) {
     const int64_t o = at;
     at += (bytes + 255) / 256 * 256;
@@ -635,8 +638,9 @@ TableLayout table_layout(const nep_hparams& hp, int nd) {
   L.at_w1 = take(at, (int64_t)L.nets * L.NNp * 4);
   L.at_w0b = take(at, (int64_t)L.nets * L.NNp * L.NDp32 * 2);
   L.at_w0tb = take(at, (int64_t)L.nets * L.NDp32 * L.NNp * 2);
-  L.at_cR = take(at, (int64_t)L.T * L.T * L.nR * L.KR * 4);
+  L.at_cR = take(at, (int64_t)L.T * L.T * L.KR * round4(L.nR) * 4);
   L.at_cA = take(at, L.n_cA * 4);
+  L.at_cS = take(at, L.n_cA * 4);
   L.set_bytes = at;
   return L;
 }
@@ -653,17 +657,8 @@ DevModel model_at(const DevModel& proto, const TableLayout& L, const unsigned ch
   M.w0tb = (const uint16_t*)(base + L.at_w0tb);
   M.cR = (const float*)(base + L.at_cR);
   M.cA = (const float*)(base + L.at_cA);
-  for (int ng = 0; ng < 8; ++ng) {
-    M.cA_off[ng] = -1;
-    M.cA_pair[ng] = 0;
-  }
-  int32_t cA_max = 0;
-  for (int o = 0; o < L.n_ng; ++o) {
-    M.cA_off[L.ng_of[o]] = (int32_t)L.cA_off_of[o];
-    M.cA_pair[L.ng_of[o]] = L.cA_pair_of[o];
-    cA_max = std::max(cA_max, L.T * L.T * L.cA_pair_of[o]);
-  }
-  M.cA_max = cA_max;
+  M.cS = (const float*)(base + L.at_cS);
+  M.cA_pair = L.cA_pair;
   return M;
 }
 
@@ -681,8 +676,14 @@ int32_t estimate_capacity(double rc, double density) {
   return (m + 3) / 4 * 4;
 }
 
-void ensure_lists(nep_handle* h, int64_t N, int32_t MR, int32_t MA) {
-  if (N <= h->capN && MR <= h->MR && MA <= h->MA && h->L.nlR) return;
+// Rows of MR (and MA) slots; `batch` asks for the entries' displacements too
+// (kept from then on).
+void ensure_lists(nep_handle* h, int64_t N, int32_t MR, int32_t MA, bool batch = false) {
+  batch = batch || h->disp;
+  if (N <= h->capN && MR <= h->MR && MA <= h->MA && h->L.nlR) {
+    if (batch && !h->disp) dev_alloc(h->disp, (size_t)h->MR * h->capN);
+    return;
+  }
   if (MR > kMaxRow || MA > kMaxRow)
     throw Failure{NEP_E_NEIGHBOR_OVERFLOW, "neighbour rows longer than 65535 entries"};
   h->free_lists();
@@ -691,6 +692,7 @@ void ensure_lists(nep_handle* h, int64_t N, int32_t MR, int32_t MA) {
   dev_alloc(h->L.nlR, (size_t)MR * cap); dev_alloc(h->L.cdR, (size_t)MR * cap);
   dev_alloc(h->L.revR, (size_t)MR * cap);
   dev_alloc(h->P, (size_t)MR * cap);
+  if (batch) dev_alloc(h->disp, (size_t)MR * cap);
   h->MR = MR;
   h->MA = MA;
   h->L.MR = MR;
@@ -731,7 +733,7 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     dev_alloc(h->key, c); dev_alloc(h->perm, c); dev_alloc(h->inv, c);
     dev_alloc(h->out_e, c); dev_alloc(h->out_f, 3 * c); dev_alloc(h->out_w, 9 * c);
     dev_alloc(h->q, (size_t)c * M.NDp); dev_alloc(h->fp, (size_t)c * M.NDp);
-    dev_alloc(h->U, c); dev_alloc(h->sums, (size_t)M.nA * M.NB * c);
+    dev_alloc(h->U, c); dev_alloc(h->sums, (size_t)sums_floats(M) * c);
     dev_alloc(h->F, 3 * c); dev_alloc(h->W, 9 * c);
     h->rows_cap = rows_length(c, M.T);
     dev_alloc(h->rows, h->rows_cap);
@@ -788,6 +790,7 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.rcR2 = h->hp.rc_radial * h->hp.rc_radial;
   b.rcA2 = h->hp.rc_angular * h->hp.rc_angular;
   b.overflow = h->flags;
+  b.disp = pp.batch ? h->disp : nullptr;
   b.wide_rows = 0;
   for (const StructInfo& st : pp.sts)
     if (st.mode != kModeCells) b.wide_rows = 1;
@@ -808,6 +811,7 @@ EvalArgs eval_args(nep_handle* h, const Prepared& pp, const DevModel& M) {
   a.U = h->U;
   a.sums = h->sums;
   a.P = h->P;
+  a.disp = h->disp;
   a.F = h->F;
   a.W = h->W;
   a.rows = h->rows;
@@ -851,7 +855,7 @@ Prepared prepare_batch(nep_handle* h, int32_t S, const int64_t* offs, const doub
   int32_t MA = h->hp.max_nb_angular ? h->hp.max_nb_angular : estimate_capacity(h->hp.rc_angular, max_density);
   MR = std::max(MR, h->MR);
   MA = std::max(MA, h->MA);
-  ensure_lists(h, N, MR, MA);
+  ensure_lists(h, N, MR, MA, pp.batch);
   // candidate rows at r_list (= r_c^R, or r_c^R + skin)
   const int32_t MV = r_list > h->hp.rc_radial ? estimate_capacity(r_list, max_density) : MR;
   ensure_verlet(h, N, std::max(MV, h->V.MR));
@@ -962,110 +966,32 @@ void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, c
   build_rows_checked(h, pp, b, s, check);
 }
 
-void set_groups(EvalArgs& a, int NG, int block, int nA, int lanes) {
-  a.NG = NG;
-  a.ngroups = (nA + NG - 1) / NG;
-  a.block = block;
-  a.lanes = lanes;
-}
+// Kernel shape of a call.  A quad of lanes per atom uses the lanes best (a row
+// of 42 entries takes 11 steps of 4, 95 % of them live); four quads take a
+// quarter of the steps, with more of them past the row's end and the per-atom
+// work repeated, and win while one quad per atom leaves SIMDs without a wave:
+// below 1024 waves of 16 atoms.  Descriptor and force kernels in us, one quad
+// against four: the 4-species alloy 54 : 32 at 4,000 atoms, 56 : 49 at 10,976,
+// 80 : 82 at 23,328; l_max = 6 62 : 45 at 8,192 and 98 : 119 at 27,648; a batch's
+// whole pass 111 : 95 at 6,532 atoms and 117 : 130 at 13,064.  A batch keeps the
+// shape of the handle's first batch, so that a structure's result does not
+// depend on the others in it.
+constexpr int64_t kQuadAtoms = 16384;
 
-bool autotune_enabled() {
-  const char* e = std::getenv("NEP_AUTOTUNE");
-  return !(e && e[0] == '0');
-}
-
-// Project autotuner: on the first evaluation of a shape, time every admissible
-// (angular group size, block size, lanes per atom) of the descriptor and
-// partial-force kernels on the actual rows (one warm-up and two timed
-// launches each, HIP events on the work stream) and keep the fastest.  The
-// choice is fixed per handle afterwards, so repeated calls stay bitwise
-// reproducible.
-void autotune(nep_handle* h, const Prepared& pp, hipStream_t s) {
+const Tuning& pick_shape(nep_handle* h, const Prepared& pp) {
   Tuning& t = h->tune[pp.batch ? 1 : 0];
-  if (t.done) return;
-  const int nA = h->M.nA, L = h->M.L;
-  t.NG_desc = t.NG_force = angular_group_size(nA, L);
-  t.block_desc = t.block_force = kBlock;
-  t.lanes_desc = t.lanes_force = 4;
+  if (!t.done || !pp.batch) t.quads = pp.N < kQuadAtoms ? 4 : 1;
   t.done = true;
-  if (!autotune_enabled()) return;
-  EvalArgs a = eval_args(h, pp, h->M);
-  hipEvent_t e0, e1;
-  HIPCHK(hipEventCreate(&e0));
-  HIPCHK(hipEventCreate(&e1));
-  auto time_it = [&](bool force, int ng, int block, int lanes) {
-    set_groups(a, ng, block, nA, lanes);
-    float best = 1e30f;
-    for (int rep = 0; rep < 3; ++rep) {
-      HIPCHK(hipEventRecord(e0, s));
-      bool ok = force ? launch_partial_forces(a, s) : launch_descriptor(a, s);
-      HIPCHK(hipEventRecord(e1, s));
-      HIPCHK(hipEventSynchronize(e1));
-      if (!ok) return 1e30f;
-      float ms = 0;
-      HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-      if (rep > 0) best = std::min(best, ms);
-    }
-    return best;
-  };
-  const int blocks[] = {128, 256};
-  const int lane_opts[] = {1, 4};
-  auto search = [&](bool force, int& ng_out, int& block_out, int& lanes_out) {
-    float best = 1e30f;
-    for (int ng : angular_group_options(nA, L))
-      for (int bl : blocks)
-        for (int ln : lane_opts) {
-          if (eval_lds_bytes(h->M, bl) > 64 * 1024) continue;
-          float ms = time_it(force, ng, bl, ln);
-          if (ms < best) {
-            best = ms;
-            ng_out = ng;
-            block_out = bl;
-            lanes_out = ln;
-          }
-        }
-  };
-  search(false, t.NG_desc, t.block_desc, t.lanes_desc);
-  // the partial-force kernel reads dU/dq: run the chosen descriptor pass and the network once
-  set_groups(a, t.NG_desc, t.block_desc, nA, t.lanes_desc);
-  launch_descriptor(a, s);
-  launch_mlp(a, s);
-  search(true, t.NG_force, t.block_force, t.lanes_force);
-  // the gather reads the partial forces: run the chosen force pass once, then time lanes 1 and 4
-  set_groups(a, t.NG_force, t.block_force, nA, t.lanes_force);
-  launch_partial_forces(a, s);
-  {
-    float best = 1e30f;
-    for (int ln : lane_opts) {
-      a.lanes = ln;
-      float ms_best = 1e30f;
-      for (int rep = 0; rep < 3; ++rep) {
-        HIPCHK(hipEventRecord(e0, s));
-        launch_gather_forces(a, false, s);
-        HIPCHK(hipEventRecord(e1, s));
-        HIPCHK(hipEventSynchronize(e1));
-        float ms = 0;
-        HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-        if (rep > 0) ms_best = std::min(ms_best, ms);
-      }
-      if (ms_best < best) {
-        best = ms_best;
-        t.lanes_gather = ln;
-      }
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  return t;
 }
 
 // Descriptors, network, partial forces and the force gather; the per-atom
 // virial only when `virial` (MD steps without a thermo row skip it).
 void forces(nep_handle* h, const Prepared& pp, hipStream_t s, const DevModel* model = nullptr,
             bool virial = true, const MDArgs* kick = nullptr) {
-  autotune(h, pp, s);
-  const Tuning& t = h->tune[pp.batch ? 1 : 0];
+  const Tuning& t = pick_shape(h, pp);
   EvalArgs a = eval_args(h, pp, model ? *model : h->M);
-  set_groups(a, t.NG_desc, t.block_desc, h->M.nA, t.lanes_desc);
+  a.quads = t.quads;
   {
     Stage st(h, "descriptor", s);
     if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
@@ -1074,7 +1000,6 @@ void forces(nep_handle* h, const Prepared& pp, hipStream_t s, const DevModel* mo
     Stage st(h, "mlp", s);
     launch_mlp(a, s);
   }
-  set_groups(a, t.NG_force, t.block_force, h->M.nA, t.lanes_force);
   {
     Stage st(h, "partial_forces", s);
     if (!launch_partial_forces(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no force kernel for this shape"};
@@ -1195,7 +1120,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     h->batch_sts = pp.sts;
     h->batch_cells = pp.n_cells;
   }
-  autotune(h, pp, s);
+  pick_shape(h, pp);
   // everything the captured kernels hold by value or by address
   std::vector<unsigned char> key;
   auto put = [&](const void* p, size_t n) {
@@ -1703,8 +1628,7 @@ int nep_create(const nep_hparams* hp, const double* params, size_t n, nep_handle
     h->nets = hp->nn_per_type ? hp->n_types : 1;
     upload_model(h, params, h->main);
     HIPCHK(loss_scratch_address(h->device, &h->scratch));
-    // LDS budget of the pair kernels: coefficient tables + per-thread slots
-    if (eval_lds_bytes(h->M, kBlock) > 64 * 1024)
+    if (!tables_fit(h->M))
       throw Failure{NEP_E_UNSUPPORTED, "n_types x basis sizes too large for the LDS budget"};
   } catch (const Failure& f) {
     delete h;
@@ -2092,9 +2016,8 @@ int nep_descriptors(nep_handle* h, int64_t N, const double* pos, const int32_t* 
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     order_and_build(h, pp, h->pos_ext, h->types_ext, s, true);
-    autotune(h, pp, s);
     EvalArgs a = eval_args(h, pp, h->M);
-    set_groups(a, h->tune[0].NG_desc, h->tune[0].block_desc, h->M.nA, h->tune[0].lanes_desc);
+    a.quads = pick_shape(h, pp).quads;
     if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
     double* d_q = nullptr;
     dev_alloc(d_q, (size_t)N * h->nd);
@@ -2124,12 +2047,11 @@ int nep_latent(nep_handle* h, int64_t N, const double* pos, const int32_t* types
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     order_and_build(h, pp, h->pos_ext, h->types_ext, s, true);
-    autotune(h, pp, s);
     const int NN = h->hp.n_neurons;
     dev_alloc(d_lat, (size_t)N * NN);
     dev_alloc(d_out, (size_t)N * NN);
     EvalArgs a = eval_args(h, pp, h->M);
-    set_groups(a, h->tune[0].NG_desc, h->tune[0].block_desc, h->M.nA, h->tune[0].lanes_desc);
+    a.quads = pick_shape(h, pp).quads;
     if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
     a.latent = d_lat;
     launch_mlp(a, s);
@@ -2892,8 +2814,7 @@ int nep_get_tuning(const nep_handle* h, int32_t batch, int32_t out[7]) {
   if (!h || !out || (batch != 0 && batch != 1))
     return fail(nullptr, {NEP_E_INVALID_ARG, "handle, batch in {0, 1} and out[7] are required"});
   const Tuning& t = h->tune[batch];
-  const int32_t v[7] = {t.NG_desc, t.block_desc, t.lanes_desc, t.NG_force, t.block_force,
-                        t.lanes_force, t.lanes_gather};
+  const int32_t v[7] = {h->M.nA, kBlock, t.quads, h->M.nA, kBlock, t.quads, t.lanes_gather};
   for (int k = 0; k < 7; ++k) out[k] = t.done ? v[k] : 0;
   return NEP_OK;
 }

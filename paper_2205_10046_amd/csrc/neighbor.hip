@@ -826,11 +826,16 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
 // V.fmap of that candidate entry, written in place.  kRevLanes lanes per atom
 // take exact entries p = s, s + 4, ..., so a wave writes whole 64-byte runs of
 // a row; a lane loads the words of kFilterChunk entries, then their map
-// entries, then writes them.
+// entries, then writes them.  For a batch (DISP) it also writes every
+// entry's float32 displacement and species (as bits), read by each parameter
+// set's passes.
 constexpr int kRevLanes = 4;
 
-__global__ void __launch_bounds__(kBlock) k_reverse_from_candidates(int64_t N, Lists V, Lists L,
-                                                                    int32_t* __restrict__ err) {
+template <bool DISP>
+__global__ void __launch_bounds__(kBlock) k_reverse_from_candidates(
+    int64_t N, Lists V, Lists L, const double* __restrict__ pos, const int32_t* __restrict__ types,
+    const int32_t* __restrict__ sid, const StructInfo* __restrict__ structs, float4* __restrict__ disp,
+    int32_t* __restrict__ err) {
   constexpr int G = kRevLanes, U = kFilterChunk;
   const int sub = threadIdx.x & (G - 1);
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
@@ -840,6 +845,14 @@ __global__ void __launch_bounds__(kBlock) k_reverse_from_candidates(int64_t N, L
   int32_t* __restrict__ lrev = L.revR;
   const int nn = min(L.nnR[i], L.MR);
   bool broken = false;
+  StructInfo st;
+  double xi = 0.0, yi = 0.0, zi = 0.0;
+  if (DISP) {
+    st = structs[sid[i]];
+    xi = pos[i];
+    yi = pos[N + i];
+    zi = pos[2 * N + i];
+  }
   // the words of chunk p0 + U G are loaded while chunk p0's map entries are in flight
   int32_t jq[U], rq[U];
   auto load_words = [&](int p0) __attribute__((always_inline)) {
@@ -874,6 +887,38 @@ __global__ void __launch_bounds__(kBlock) k_reverse_from_candidates(int64_t N, L
         g[u] = 0;
       }
       lrev[(int64_t)p * N + i] = min(g[u], L.MR - 1);
+    }
+    if constexpr (DISP) {
+      double px[U], py[U], pz[U];
+      int32_t t[U];
+      uint16_t code[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // past the row: word 0, an atom in bounds
+        px[u] = pos[j[u]];
+        py[u] = pos[N + j[u]];
+        pz[u] = pos[2 * N + j[u]];
+        t[u] = types[j[u]];
+        code[u] = kCodeCenter;
+        if (st.mode == kModeImages && p0 + u * G < nn) code[u] = L.cdR[(int64_t)(p0 + u * G) * N + i];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int p = p0 + u * G;
+        if (p >= nn) continue;
+        double Dx, Dy, Dz;
+        {
+#pragma clang fp contract(off)
+          Dx = px[u] - xi;
+          Dy = py[u] - yi;
+          Dz = pz[u] - zi;
+        }
+        int n0, n1, n2, oa, ob, oc;
+        min_image(st, Dx, Dy, Dz, n0, n1, n2);
+        split_code(code[u], oa, ob, oc);
+        double dx, dy, dz;
+        image_disp(st, Dx, Dy, Dz, n0 + oa, n1 + ob, n2 + oc, dx, dy, dz);
+        disp[(int64_t)p * N + i] = make_float4((float)dx, (float)dy, (float)dz, __int_as_float(t[u]));
+      }
     }
   }
   if (broken) atomicExch(err, 1);
@@ -968,8 +1013,13 @@ void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, c
   else
     hipLaunchKernelGGL(k_filter_rows<false>, grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
                        st0, V, b.rcR2, b.rcA2, L, b.overflow);
-  hipLaunchKernelGGL(k_reverse_from_candidates, grid_for(b.N * kRevLanes), dim3(kBlock), 0, s,
-                     b.N, V, L, b.overflow + 2);
+  if (b.disp)
+    hipLaunchKernelGGL((k_reverse_from_candidates<true>), grid_for(b.N * kRevLanes), dim3(kBlock), 0, s, b.N, V, L,
+                       b.pos, b.types, b.sid, b.structs, b.disp, b.overflow + 2);
+  else
+    hipLaunchKernelGGL((k_reverse_from_candidates<false>), grid_for(b.N * kRevLanes), dim3(kBlock), 0, s, b.N, V, L,
+                       (const double*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr,
+                       (const StructInfo*)nullptr, (float4*)nullptr, b.overflow + 2);
 }
 
 // flag = any atom whose displacement since the last build, plus horizon

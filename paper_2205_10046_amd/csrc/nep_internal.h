@@ -13,7 +13,7 @@
 //   V.*      int32/uint16 [MV][N]     candidate rows (radius r_c^R + skin), their
 //                                     reverse index and candidate -> exact map
 //   q, fp    float32 [N][ND_pad]      descriptor / dU/dq rows (network input)
-//   sums     float32 [NA*NB][N]       angular sums S_{n,k}, SoA
+//   sums     float32x4 [NT*NBT][N][4] angular sums S_{n,k} in tiles of 4 x 4 (pair.h)
 //   P        float32x4 [MR][N]        dU_i/dr_ij per radial entry, radial and
 //                                     angular parts summed (w unused)
 #pragma once
@@ -129,8 +129,6 @@ __device__ inline void entry_disp(const double* __restrict__ pos, int64_t N, int
   image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
 }
 
-// Row length of a group of NG radial functions in the angular table.
-__host__ __device__ constexpr int ng_pad(int ng) { return ng <= 2 ? ng : (ng + 3) / 4 * 4; }
 __host__ __device__ constexpr int round4(int n) { return (n + 3) / 4 * 4; }
 // Smallest stride >= n floats that is 4 mod 64 (bank-spread species pairs).
 __host__ __device__ constexpr int pair_stride(int n) { return n + ((4 - n % 64) + 64) % 64; }
@@ -140,18 +138,18 @@ __host__ __device__ constexpr int pair_stride(int n) { return n + ((4 - n % 64) 
 // functions so kernels never test n < n_max + 1.
 struct DevModel {
   int32_t T, nR, KR, nA, KA, L, NB, ND, NDp, NN, nets, has4b, has5b;
-  int32_t cA_max;           // largest angular table (floats) over the group sizes
   float rcR, rcA;
   const float* b1;          // the output bias b1, one float in device memory
-  const float* cR;          // [T][T][nR][KR]
-  // angular coefficients for group size NG at cA + cA_off[NG] (-1: none):
-  // [T x T species pairs, cA_pair[NG] floats apart][groups][KA][ng_pad(NG)],
-  // the NG functions of a group contiguous (zero beyond n_A), so one aligned
-  // vector read serves a whole group; the pair stride is 4 mod 64 floats so
-  // lanes reading different species pairs fall into different LDS banks
+  const float* cR;          // [T][T][KR][n_R rounded up to 4], zero beyond n_R
+  // angular coefficients [T x T species pairs, cA_pair floats apart][KA][n_A
+  // rounded up to 4], zero beyond n_A, so the functions of a tile are aligned
+  // vector reads; the pair stride is 4 mod 64 floats so lanes reading
+  // different species pairs fall into different LDS banks
   const float* cA;
-  int32_t cA_off[8];
-  int32_t cA_pair[8];
+  // the same for the force pass, the basis f_k = (T_k + 1) f_c / 2 written as a
+  // Chebyshev series: c_0 + sum_k c_k / 2, then c_k / 2
+  const float* cS;
+  int32_t cA_pair;
   int32_t NNp;              // N_neu rounded up to 32 (zero-padded neurons)
   int32_t NDp32;            // N_des rounded up to 32
   const float* w0;          // [nets][NNp][ND]   network weights w0, row = neuron

@@ -1,7 +1,5 @@
 // nep_kernels.h -- argument blocks and launchers of the NEP kernels.
 #pragma once
-#include <vector>
-
 #include "nep_internal.h"
 
 namespace nep {
@@ -26,6 +24,7 @@ struct BuildArgs {
   int32_t* overflow;          // flags: [0] radial row, [1] angular row, [2] rev error,
                               // [5] candidate row overflow (max counts)
   const int32_t* gate;        // rebuild kernels run only when *gate != 0 (NULL: always)
+  float4* disp = nullptr;     // batches: displacement and species of every exact entry, [MR][N]
   int32_t wide_rows = 0;      // some structure has no cells: its rows come from k_build_rows_wide
   // optional: velocities and caller indices permuted with the positions
   const double* vel_src = nullptr;
@@ -45,8 +44,9 @@ struct EvalArgs {
   float* q;                   // [N][NDp]
   float* fp;                  // [N][NDp]
   float* U;                   // [N]
-  float* sums;                // [nA_pad * NB][N]
+  float* sums;                // [tiles][N][4][4], see pair.h
   float4* P;                  // [MR][N] dU_i/dr_ij per radial entry
+  const float4* disp;         // [MR][N] displacement and species (as bits) per entry (batches)
   float* F;                   // [3][N] internal
   float* W;                   // [9][N] internal
   float* latent;              // [N][N_neu] w1_mu h_mu of every atom, or NULL
@@ -57,11 +57,9 @@ struct EvalArgs {
   double kick_dt;
   const int32_t* rows;        // network row order, [rows_len]
   int64_t rows_len;
-  int32_t ngroups;            // angular radial-function groups
-  int32_t NG;                 // group size
-  int32_t lanes;              // lanes per atom of the pair kernels (1 or 4)
+  int32_t quads;              // quads of lanes per atom of the pair kernels (1 or 4)
+  int32_t lanes;              // lanes per atom of the gather (1 or 4)
   int32_t mlp_bf16;
-  int32_t block;              // threads per block of the pair kernels (0 = 256)
   int32_t batch;              // several structures: geometry from structs[sid]
   StructInfo st0;             // the geometry when batch == 0
 };
@@ -106,13 +104,12 @@ void launch_type_rows(const int32_t* types, int64_t N, int32_t T, int32_t per_ty
                       int32_t* tblk, int32_t* tex, int32_t* toff, int32_t* rows,
                       int64_t rows_len, const int32_t* gate, hipStream_t s);
 
-// descriptor.hip / force.hip: return false if no kernel exists for (NG, L)
+// descriptor.hip / force.hip: return false if no kernel exists for the model
 bool launch_descriptor(const EvalArgs& a, hipStream_t s);
 bool launch_partial_forces(const EvalArgs& a, hipStream_t s);
 void launch_gather_forces(const EvalArgs& a, bool virial, hipStream_t s);
-size_t eval_lds_bytes(const DevModel& M, int block);
-int angular_group_size(int nA, int L);
-std::vector<int> angular_group_options(int nA, int L);
+// Floats per atom of the angular sums (4 x 4 tiles over n_A and the polynomials).
+inline int64_t sums_floats(const DevModel& M) { return (int64_t)((M.nA + 3) / 4) * ((M.NB + 3) / 4) * 16; }
 
 // mlp.hip
 void launch_mlp(const EvalArgs& a, hipStream_t s);
@@ -138,10 +135,9 @@ void launch_inverse_perm(const int32_t* perm, int64_t N, int32_t* inv, hipStream
 struct TableLayout {
   int32_t nets, NN, NNp, ND, NDp32, T, nR, KR, nA, KA;
   int64_t off_b1, off_cR, off_cA;           // in the float64 parameter vector
-  int32_t n_ng;                             // admissible angular group sizes
-  int32_t ng_of[4], cA_pair_of[4];
-  int64_t cA_off_of[4], n_cA;               // floats, per group size and in all
-  int64_t at_w0, at_w0t, at_b0, at_w1, at_w0b, at_w0tb, at_cR, at_cA, set_bytes;
+  int32_t cA_pair;                          // floats between species pairs of the angular table
+  int64_t n_cA;                             // its floats in all
+  int64_t at_w0, at_w0t, at_b0, at_w1, at_w0b, at_w0tb, at_cR, at_cA, at_cS, set_bytes;
 };
 int64_t table_elements(const TableLayout& L);
 void launch_model_tables(const double* params, int64_t npar, int32_t P, const TableLayout& L,

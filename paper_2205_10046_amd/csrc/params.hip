@@ -66,34 +66,41 @@ __global__ void k_model_tables(const double* __restrict__ params, int64_t npar, 
     return;
   }
   k -= n_wb;
-  // radial coefficients c^R [T][T][nR][KR]
-  const int64_t n_cR = (int64_t)L.T * L.T * L.nR * L.KR;
+  // radial coefficients c^R [T][T][KR][n_R rounded up to 4]
+  const int wR = round4(L.nR);
+  const int64_t n_cR = (int64_t)L.T * L.T * L.KR * wR;
   if (k < n_cR) {
-    ((float*)(out + L.at_cR))[k] = (float)p[L.off_cR + k];
+    const int n = (int)(k % wR), kk = (int)(k / wR % L.KR);
+    const int64_t a = k / wR / L.KR;
+    ((float*)(out + L.at_cR))[k] = n < L.nR ? (float)p[L.off_cR + (a * L.nR + n) * L.KR + kk] : 0.f;
     return;
   }
   k -= n_cR;
-  // angular coefficients, one table per group size NG:
-  // [T x T pairs, pair stride apart][groups][KA][ng_pad(NG)]
+  // angular coefficients [T x T pairs, pair stride apart][KA][n_A rounded up to 4]
+  // and their Chebyshev series
   if (k < L.n_cA) {
-    int o = 0;
-    while (o + 1 < L.n_ng && k >= L.cA_off_of[o + 1]) ++o;
-    const int ng = L.ng_of[o], w = ng_pad(ng), ps = L.cA_pair_of[o];
-    const int64_t r = k - L.cA_off_of[o];
-    const int a = (int)(r / ps), q = (int)(r % ps);
-    float x = 0.f;
-    if (q < ((L.nA + ng - 1) / ng) * L.KA * w) {
-      const int grp = q / (L.KA * w), rem = q % (L.KA * w), kk = rem / w, lane = rem % w;
-      const int n = grp * ng + lane;
-      if (lane < ng && n < L.nA) x = (float)p[L.off_cA + ((int64_t)a * L.nA + n) * L.KA + kk];
+    const int w = round4(L.nA);
+    const int a = (int)(k / L.cA_pair), q = (int)(k % L.cA_pair), kk = q / w, n = q % w;
+    float x = 0.f, y = 0.f;
+    if (kk < L.KA && n < L.nA) {
+      const double* c = p + L.off_cA + ((int64_t)a * L.nA + n) * L.KA;
+      x = (float)c[kk];
+      if (kk > 0) {
+        y = 0.5f * x;
+      } else {
+        float sum = 0.f;
+        for (int v = L.KA - 1; v > 0; --v) sum += 0.5f * (float)c[v];
+        y = x + sum;
+      }
     }
     ((float*)(out + L.at_cA))[k] = x;
+    ((float*)(out + L.at_cS))[k] = y;
   }
 }
 
 int64_t table_elements(const TableLayout& L) {
   return (int64_t)L.nets * L.NNp * L.ND + (int64_t)L.nets * L.NNp + (int64_t)L.nets * L.NNp * L.NDp32 +
-         (int64_t)L.T * L.T * L.nR * L.KR + L.n_cA;
+         (int64_t)L.T * L.T * L.KR * round4(L.nR) + L.n_cA;
 }
 
 void launch_model_tables(const double* params, int64_t npar, int32_t P, const TableLayout& L,

@@ -528,7 +528,7 @@ class Handle:
 
 
     def tuning(self, batch=False):
-        """Kernel shapes fixed by the autotuner (zeros before the first evaluation)."""
+        """Kernel shapes of the last evaluation (zeros before the first one)."""
         out = np.zeros(7, np.int32)
         self._check(load().nep_get_tuning(self._h, 1 if batch else 0, _ptr(out, C.c_int32)))
         keys = ("ng_desc", "block_desc", "lanes_desc", "ng_force", "block_force", "lanes_force",
