@@ -256,6 +256,13 @@ Geometry make_geometry(const double* box, const int32_t* pbc, int64_t n_atoms, d
       nc[k] = std::min(nc[k], 1024);
       total *= nc[k];
     }
+    // a box that is mostly empty: larger cells, so that the passes over the cells do
+    // not outweigh those over the atoms
+    while (total > 4 * n_atoms + 64) {
+      int32_t& widest = *std::max_element(nc, nc + 3);
+      total = total / widest * (widest / 2);
+      widest /= 2;
+    }
     if (n_atoms > 256 && total > 1 && total < (1 << 28)) {
       st.mode = kModeCells;
       for (int k = 0; k < 3; ++k) st.ncell[k] = nc[k];
@@ -791,9 +798,8 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.rcA2 = h->hp.rc_angular * h->hp.rc_angular;
   b.overflow = h->flags;
   b.disp = pp.batch ? h->disp : nullptr;
-  b.wide_rows = 0;
-  for (const StructInfo& st : pp.sts)
-    if (st.mode != kModeCells) b.wide_rows = 1;
+  b.n_struct = (int32_t)pp.sts.size();
+  for (const StructInfo& st : pp.sts) (st.mode == kModeCells ? b.cell_rows : b.wide_rows) = 1;
   return b;
 }
 
@@ -922,16 +928,13 @@ void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, h
     }
     {
       Stage st(h, "neighbor_rows", s);
-      launch_build_rows(b, pp.geo.st, pp.batch, h->V, h->L, s);
+      launch_build_rows(b, h->V, h->L, s);
     }
-    launch_check_rows(pp.N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, h->flags + 6, s);
     int32_t* fl = (int32_t*)(h->pinned + kPinFlags);
     HIPCHK(hipMemcpyAsync(fl, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (fl[3]) throw Failure{NEP_E_INVALID_ARG, "an atom type is out of range"};
     if (fl[4]) throw Failure{NEP_E_NONFINITE, "positions contain NaN or Inf"};
-    // the candidate rows are at r_c^R here: their overflow count is the radial one
-    fl[0] = std::max(fl[0], fl[5]);
     if (fl[0] == 0 && fl[1] == 0) {
       // without truncated rows every entry has its reverse entry
       if (fl[2]) throw Failure{NEP_E_HIP, "internal error: neighbour rows are not symmetric"};
@@ -2628,7 +2631,7 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       {
         Stage st(h, "neighbor_rows", s);
         BuildArgs b2 = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
-        launch_build_rows(b2, pp.geo.st, pp.batch, h->V, h->L, s);
+        launch_build_rows(b2, h->V, h->L, s);
       }
       forces(h, pp, s, nullptr, thermo_every > 0 && step % thermo_every == 0);
       md.pos = h->pos;
@@ -2651,7 +2654,6 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
     HIPCHK(hipMemcpyAsync(fl, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     if (fl[4]) throw Failure{NEP_E_NONFINITE, "positions became non-finite during the run"};
-    fl[0] = std::max(fl[0], fl[5]);  // candidate rows at r_c^R: the same count
     if (fl[2] && !(fl[0] || fl[1]))
       throw Failure{NEP_E_HIP, "internal error: neighbour rows are not symmetric"};
     if (!(fl[0] || fl[1])) check_row_flag(fl[6]);

@@ -20,6 +20,8 @@
 //      search on the sorted candidate rows (once per candidate build) and the
 //      candidate -> exact position map of every filter, so the force pass
 //      can gather dU_j/dr_ji without atomics.
+#include <algorithm>
+
 #include "nep_kernels.h"
 
 namespace nep {
@@ -80,12 +82,14 @@ __global__ void k_cell_key(const double* __restrict__ pos, int64_t N,
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= N || gated_off(gate)) return;
   const StructInfo& st = structs[sid[e]];
-  int k = st.cell_off;
-  if (st.mode == kModeCells) {
-    int cx, cy, cz;
-    cell_coords(st, pos[e], pos[N + e], pos[2 * N + e], cx, cy, cz);
-    k += (cz * st.ncell[1] + cy) * st.ncell[0] + cx;
+  if (st.mode != kModeCells) {  // one cell, in caller order (k_cell_scatter)
+    key[e] = st.cell_off;
+    if (e == st.start) cell_count[st.cell_off] = (int32_t)st.count;
+    return;
   }
+  int cx, cy, cz;
+  cell_coords(st, pos[e], pos[N + e], pos[2 * N + e], cx, cy, cz);
+  const int k = st.cell_off + (cz * st.ncell[1] + cy) * st.ncell[0] + cx;
   key[e] = k;
   atomicAdd(&cell_count[k], 1);
 }
@@ -117,13 +121,21 @@ __global__ void __launch_bounds__(1024) k_scan_1block(const int32_t* __restrict_
   }
 }
 
-__global__ void k_cell_scatter(const int32_t* __restrict__ key, int64_t N,
-                               const int32_t* __restrict__ cell_start,
+// A structure without cells keeps its order: its atoms come in caller order
+// on the first call and stay so, and its cell needs no slots and no sort (its
+// cell_fill stays 0).
+__global__ void k_cell_scatter(const int32_t* __restrict__ key, int64_t N, const int32_t* __restrict__ sid,
+                               const StructInfo* __restrict__ structs, const int32_t* __restrict__ cell_start,
                                int32_t* __restrict__ cell_fill, int32_t* __restrict__ perm,
                                const int32_t* gate) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= N || gated_off(gate)) return;
+  const StructInfo& st = structs[sid[e]];
   int k = key[e];
+  if (st.mode != kModeCells) {
+    perm[cell_start[k] + (e - st.start)] = (int32_t)e;
+    return;
+  }
   int slot = atomicAdd(&cell_fill[k], 1);
   perm[cell_start[k] + slot] = (int32_t)e;
 }
@@ -141,6 +153,7 @@ constexpr int kSortPerLane = 16;
 
 __global__ void __launch_bounds__(kBlock) k_cell_sort(const int32_t* __restrict__ cell_start,
                                                       const int32_t* __restrict__ cell_count,
+                                                      const int32_t* __restrict__ cell_fill,
                                                       int32_t n_cells, const int32_t* __restrict__ ext,
                                                       int32_t* __restrict__ perm, const int32_t* gate) {
   const int lane = threadIdx.x & 63;
@@ -148,7 +161,7 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort(const int32_t* __restrict_
   if (c >= n_cells || gated_off(gate)) return;  // the lanes of a wave leave together
   int32_t* p = perm + cell_start[c];
   const int n = cell_count[c];
-  if (n <= 1) return;
+  if (n <= 1 || cell_fill[c] == 0) return;  // (no slots taken: already in order)
   if (n > 64 * kSortPerLane) {
     if (lane != 0) return;
     for (int a = 1; a < n; ++a) {
@@ -255,167 +268,363 @@ __device__ inline int stencil_1d(int c, int n, int periodic, int* out) {
   return k;
 }
 
-// Candidate rows of the atoms of cell-mode structures, kCellLanes lanes per
-// atom: the 27 stencil cells in order, each cell's atoms taken kCellLanes at
-// a time (lane s the (k0 + s)-th), each accepted one placed by a count over
-// the atom's lanes' ballot bits, so the row is the one a single lane's scan
-// writes (cells in stencil order, atoms in cell order).  Atoms of structures
-// without cells take their rows from k_build_rows_wide.
-constexpr int kCellLanes = 4;
+// Set bits of m below this lane.
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
 
-__global__ void __launch_bounds__(kBlock) k_build_rows(
-    const double* __restrict__ pos, int64_t N, const int32_t* __restrict__ sid,
-    const StructInfo* __restrict__ structs, const int32_t* __restrict__ cell_start,
-    const int32_t* __restrict__ cell_count, double rc2, Lists V, int32_t* __restrict__ overflow,
-    const int32_t* gate) {
-  constexpr int G = kCellLanes;
-  const int sub = threadIdx.x & (G - 1);
-  const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
-  if (i >= N || gated_off(gate)) return;  // the lanes of an atom leave together
-  const StructInfo st = structs[sid[i]];
+// Where a row builder puts the members it finds.  EXACT: the exact rows of a
+// call without a skin, the angular-range members straight into L and the
+// others parked in V's row (it is unused by such a call) until the number of
+// angular ones is known; else the candidate rows V (radius r_c^R + skin).
+// Members arrive in row order, so each part comes out sorted by (j, image).
+template <bool EXACT>
+struct RowSink {
+  const Lists &V, &L;
+  const int64_t N, i;
+  const bool images;
+  int32_t na = 0, no = 0;  // members found so far: angular, others (all of them: no, unless EXACT)
+  __device__ __forceinline__ void put(bool angular, int32_t p, int32_t j, uint16_t code) const {
+    const int64_t e = (int64_t)p * N + i;
+    if (EXACT && angular) {
+      if (p >= L.MR) return;
+      L.nlR[e] = j;
+      if (images) L.cdR[e] = code;
+    } else {
+      if (p >= V.MR) return;
+      V.nlR[e] = j;
+      if (!EXACT || images) V.cdR[e] = code;
+    }
+  }
+  // after the last member, by the G lanes of the atom together
+  template <int G>
+  __device__ __forceinline__ void finish(int sub, int32_t* overflow) const {
+    if constexpr (EXACT) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the parked members are other lanes' stores
+      const int32_t move = min(no, min(V.MR, L.MR - min(na, L.MR)));
+      for (int32_t p = sub; p < move; p += G) {
+        const int64_t from = (int64_t)p * N + i, to = (int64_t)(na + p) * N + i;
+        L.nlR[to] = V.nlR[from];
+        if (images) L.cdR[to] = V.cdR[from];
+      }
+      if (sub == 0) {
+        L.nnR[i] = na + no;
+        L.nnA[i] = na;
+        if (na + no > L.MR) atomicMax(&overflow[0], na + no);
+        if (na > L.MA) atomicMax(&overflow[1], na);
+      }
+    } else if (sub == 0) {
+      V.nnR[i] = no;
+      if (no > V.MR) atomicMax(&overflow[5], no);
+    }
+  }
+};
+
+// Rows of the atoms of cell-mode structures.  A block takes the atoms of one
+// cell, G lanes each.  The atoms of the (up to 27) stencil cells are
+// staged in LDS once, as float32 positions relative to one atom of the cell,
+// in increasing internal index; every lane group walks them G at a
+// time and lists those within the cutoff plus a bound of the float32 error,
+// in order (ballot counts); the listed ones, about one in six, then take the
+// float64 membership test that decides (the test is the same for every
+// builder, so the rows are those of a sequential scan of the cells).
+// Bound by instruction issue: the float64 tests and the staging's image
+// arithmetic, then the walk.  A walk of each atom over its stencil, four
+// lanes to it, was 510 dependent position loads and float64 tests per atom of
+// the 4-species alloy: 179 us for 131,072 atoms and 58 us more to part the
+// rows by cutoff, 87 us for 3,995.  This takes 136 and 14 us, parting included.
+// Members staged in LDS and stored along consecutive atoms: 132 (and 75 for
+// 66 us where the rows take a skin); one wave per cell: 158 to 162.
+constexpr int kCellStage = 1024;  // staged candidates
+constexpr int kCellList = 128;    // listed candidates of an atom between two exact passes
+
+template <bool EXACT, int G>
+__global__ void __launch_bounds__(kBlock) k_build_rows_cells(
+    const double* __restrict__ pos, int64_t N, const StructInfo* __restrict__ structs, int32_t n_struct,
+    const int32_t* __restrict__ cell_start, const int32_t* __restrict__ cell_count, int32_t n_cells, double rcR2,
+    double rcA2, Lists V, Lists L, int32_t* __restrict__ overflow, const int32_t* gate) {
+  constexpr int kCellAtoms = kBlock / G;  // atoms of a block at a time
+  __shared__ float4 stage[kCellStage];
+  __shared__ int32_t list[kCellAtoms][kCellList];
+  __shared__ int32_t c_start[27], c_first[28];
+  __shared__ float reach2[kBlock / 64];
+  if (gated_off(gate)) return;
+  const int cell = (int)xcd_block();
+  const int count = cell_count[cell], begin = cell_start[cell];
+  if ((int)blockIdx.y * kCellAtoms >= count) return;
+  // the structure this cell belongs to
+  int lo = 0, hi = n_struct - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (structs[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+  }
+  const StructInfo& st = structs[lo];
   if (st.mode != kModeCells) return;
-  const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
-  const int lane = threadIdx.x & 63;
-  const uint64_t gmask = ((1ull << G) - 1) << (lane & ~(G - 1));
-  const uint64_t below = (1ull << lane) - 1;
-  const uint16_t code0 = make_code(0, 0, 0);
-  int32_t count = 0;
-  int cx, cy, cz;
-  cell_coords(st, xi, yi, zi, cx, cy, cz);
-  int sx[3], sy[3], sz[3];
-  const int nx = stencil_1d(cx, st.ncell[0], st.pbc[0], sx);
-  const int ny = stencil_1d(cy, st.ncell[1], st.pbc[1], sy);
-  const int nz = stencil_1d(cz, st.ncell[2], st.pbc[2], sz);
-  for (int a = 0; a < nz; ++a)
-    for (int b = 0; b < ny; ++b)
-      for (int c = 0; c < nx; ++c) {
-        const int cell = st.cell_off + (sz[a] * st.ncell[1] + sy[b]) * st.ncell[0] + sx[c];
-        const int s0 = cell_start[cell], cnt = cell_count[cell];
-        for (int k0 = 0; k0 < cnt; k0 += G) {
-          const int k = k0 + sub;
-          const int64_t j = s0 + min(k, cnt - 1);
-          bool take = false;
-          if (k < cnt) {
-            double Dx, Dy, Dz;
-            {
+  const int tid = threadIdx.x, sub = tid & (G - 1), lane = tid & 63;
+  const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << (lane & ~(G - 1));
+  // the stencil: starts and running counts of its cells in increasing order
+  {
+    const int c = cell - st.cell_off, cx = c % st.ncell[0], cy = c / st.ncell[0] % st.ncell[1],
+              cz = c / (st.ncell[0] * st.ncell[1]);
+    int sx[3], sy[3], sz[3];
+    const int nx = stencil_1d(cx, st.ncell[0], st.pbc[0], sx), ny = stencil_1d(cy, st.ncell[1], st.pbc[1], sy),
+              nz = stencil_1d(cz, st.ncell[2], st.pbc[2], sz);
+    if (tid < 64) {
+      int32_t n = 0;
+      if (tid < nx * ny * nz) {
+        const int x = tid % nx, y = tid / nx % ny, z = tid / (nx * ny);
+        const int px = x == 0 ? sx[0] : (x == 1 ? sx[1] : sx[2]), py = y == 0 ? sy[0] : (y == 1 ? sy[1] : sy[2]),
+                  pz = z == 0 ? sz[0] : (z == 1 ? sz[1] : sz[2]);
+        const int k = st.cell_off + (pz * st.ncell[1] + py) * st.ncell[0] + px;
+        c_start[tid] = cell_start[k];
+        n = cell_count[k];
+      }
+      int32_t run = n;
+#pragma unroll
+      for (int off = 1; off < 32; off <<= 1) {
+        const int32_t v = __shfl_up(run, off);
+        if (lane >= off) run += v;
+      }
+      if (tid < 27) c_first[tid + 1] = run;
+      if (tid == 0) c_first[0] = 0;
+    }
+  }
+  __syncthreads();
+  const int total = c_first[27];
+  const bool any_wrap = st.pbc[0] || st.pbc[1] || st.pbc[2];
+  // float32 position relative to the cell's first atom (the nearest image of it)
+  const double rx = pos[begin], ry = pos[N + begin], rz = pos[2 * N + begin];
+  auto relative = [&](int64_t j, float& x, float& y, float& z) __attribute__((always_inline)) {
+    double dx = pos[j] - rx, dy = pos[N + j] - ry, dz = pos[2 * N + j] - rz;
+    if (any_wrap) {
+      int n0, n1, n2;
+      min_image(st, dx, dy, dz, n0, n1, n2);
+      image_disp(st, dx, dy, dz, n0, n1, n2, dx, dy, dz);
+    }
+    x = (float)dx;
+    y = (float)dy;
+    z = (float)dz;
+  };
+  // A member j of i's row is less than one cell width from i, and i from the reference,
+  // so the nearest image of j to the reference is the one next to i when two widths are
+  // at most half the box; with fewer than four cells every staged candidate is listed.
+  bool near_all = false;
+  for (int k = 0; k < 3; ++k) near_all = near_all || (st.pbc[k] && st.ncell[k] < 4);
+  const float rc2 = (float)rcR2;
+
+  for (int a0 = blockIdx.y * kCellAtoms; a0 < count; a0 += gridDim.y * kCellAtoms) {
+    const int a = a0 + tid / G;
+    const bool live = a < count;
+    const int64_t i = begin + min(a, count - 1);
+    float xi, yi, zi;
+    relative(i, xi, yi, zi);
+    const double pxi = pos[i], pyi = pos[N + i], pzi = pos[2 * N + i];
+    RowSink<EXACT> sink{V, L, N, i, false};
+    int32_t* mine = list[tid / G];
+    int listed = 0;
+    // the float64 test of the listed candidates, sixteen at a time
+    auto exact_pass = [&]() __attribute__((always_inline)) {
+      for (int q0 = 0; q0 < listed; q0 += G) {
+        const int q = q0 + sub;
+        bool ta = false, to = false;
+        int32_t j = 0;
+        if (q < listed) {
+          j = mine[q];
+          double Dx, Dy, Dz;
+          {
 #pragma clang fp contract(off)
-              Dx = pos[j] - xi;
-              Dy = pos[N + j] - yi;
-              Dz = pos[2 * N + j] - zi;
-            }
-            int n0, n1, n2;
-            min_image(st, Dx, Dy, Dz, n0, n1, n2);
-            if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
-              double dx, dy, dz;
-              image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
-              take = norm2_exact(dx, dy, dz) < rc2;
-            }
+            Dx = pos[j] - pxi;
+            Dy = pos[N + j] - pyi;
+            Dz = pos[2 * N + j] - pzi;
           }
-          const uint64_t mt = __ballot(take) & gmask;
-          if (take) {
-            const int32_t p = count + __popcll(mt & below);
-            if (p < V.MR) {
-              V.nlR[(int64_t)p * N + i] = (int32_t)j;
-              V.cdR[(int64_t)p * N + i] = code0;
-            }
+          int n0, n1, n2;
+          min_image(st, Dx, Dy, Dz, n0, n1, n2);
+          if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
+            double dx, dy, dz;
+            image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
+            const double r2 = norm2_exact(dx, dy, dz);
+            ta = EXACT && r2 < rcA2;
+            to = !ta && r2 < rcR2;
           }
-          count += __popcll(mt);
+        }
+        const uint64_t ma = __ballot(ta) & gmask, mo = __ballot(to) & gmask;
+        if (ta) sink.put(true, sink.na + lanes_below(ma), j, kCodeCenter);
+        if (to) sink.put(false, sink.no + lanes_below(mo), j, kCodeCenter);
+        sink.na += __popcll(ma);
+        sink.no += __popcll(mo);
+      }
+      listed = 0;
+    };
+    for (int base = 0; base < total; base += kCellStage) {
+      const int n = min(kCellStage, total - base);
+      __syncthreads();  // the previous stage has been walked
+      float far2 = 0.f;
+      for (int k = tid; k < n; k += kBlock) {
+        int l = 0, h = 26;  // last stencil cell whose first candidate is at or before base + k
+        while (l < h) {
+          const int mid = (l + h + 1) >> 1;
+          if (c_first[mid] <= base + k) l = mid; else h = mid - 1;
+        }
+        const int32_t j = c_start[l] + base + k - c_first[l];
+        float x, y, z;
+        relative(j, x, y, z);
+        far2 = fmaxf(far2, x * x + y * y + z * z);
+        stage[k] = make_float4(x, y, z, __int_as_float(j));
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) far2 = fmaxf(far2, __shfl_xor(far2, off));
+      if (lane == 0) reach2[tid >> 6] = far2;
+      __syncthreads();
+      // the squared float32 distance of a pair is off by less than 1e-6 (r_c^2 + 4 of
+      // the largest squared coordinate): two positions rounded to 2^-24, their
+      // difference, and three products
+      float m2 = reach2[0];
+#pragma unroll
+      for (int w = 1; w < kBlock / 64; ++w) m2 = fmaxf(m2, reach2[w]);
+      const float thr = near_all ? INFINITY : rc2 + 1e-6f * (rc2 + 8.f * (m2 + xi * xi + yi * yi + zi * zi));
+      for (int k0 = 0; k0 < n; k0 += G) {
+        const int k = k0 + sub;
+        const float4 c = stage[min(k, n - 1)];
+        const float dx = c.x - xi, dy = c.y - yi, dz = c.z - zi;
+        // (written so that a non-finite distance lists the candidate)
+        const bool near = live && k < n && !(dx * dx + dy * dy + dz * dz > thr);
+        const uint64_t m = __ballot(near) & gmask;
+        if (near) mine[listed + lanes_below(m)] = __float_as_int(c.w);
+        listed += __popcll(m);
+        if (listed > kCellList - G) {  // the same for the lanes of an atom
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          exact_pass();
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
       }
-  if (sub == 0) {
-    V.nnR[i] = count;
-    if (count > V.MR) atomicMax(overflow, count);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      exact_pass();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    if (live) sink.template finish<G>(sub, overflow);
   }
 }
 
-// Candidate rows of the atoms of structures without cells (all-pairs and
-// image modes: small cells, whose rows scan every atom of the structure, or
-// every (atom, image) pair), kBuildLanes lanes per atom.  The candidates of
-// atom i form one sequence in row order -- the atoms of the structure, or
-// the (atom, image) pairs with the image offsets innermost -- taken
-// kBuildLanes at a time (lane s the s-th of each step); each member is placed
-// by a count over the atom's lanes' ballot bits, so the row is the one a
-// sequential scan of the sequence writes: sorted by (j, image).
-constexpr int kBuildLanes = 16;
+// Rows of the atoms of structures without cells (all-pairs and image modes:
+// small cells), G lanes per atom.  The lanes take the structure's atoms j in
+// order, G at a time; the images of j within the cutoff lie between two
+// planes along every cell vector, |s_k + o_k| <= r_c / w_k with s the
+// fractional nearest-image displacement and w_k the face width, so each lane
+// lists the few offsets in that box (one or two per pair in cells of 100
+// atoms, where the structure's image range holds 125), after the lanes
+// below it; the listed (atom, image) pairs then take the float64 test of
+// every builder, G at a time, and each member is placed by a count over the
+// lanes' ballot bits.  The row is the one a sequential scan of the pairs
+// writes: sorted by (j, image).  Testing the whole image range took 2.0 ms for
+// the 132,000 atoms of 1,000 cells of the 3-species training model; this
+// takes 0.24 ms.
+constexpr int kWideList = 256;  // listed pairs of an atom between two exact passes
 
+template <bool EXACT, int G>
 __global__ void __launch_bounds__(kBlock) k_build_rows_wide(
     const double* __restrict__ pos, int64_t N, const int32_t* __restrict__ sid,
-    const StructInfo* __restrict__ structs, double rc2, Lists V, int32_t* __restrict__ overflow,
-    const int32_t* gate) {
-  constexpr int G = kBuildLanes;
+    const StructInfo* __restrict__ structs, double rcR2, double rcA2, Lists V, Lists L,
+    int32_t* __restrict__ overflow, const int32_t* gate) {
+  __shared__ int32_t list_j[kBlock / G][kWideList];
+  __shared__ uint16_t list_c[kBlock / G][kWideList];
   const int sub = threadIdx.x & (G - 1);
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
   if (i >= N || gated_off(gate)) return;  // the lanes of an atom leave together
-  if (structs[sid[i]].mode == kModeCells) return;  // k_build_rows' atoms
+  if (structs[sid[i]].mode == kModeCells) return;  // k_build_rows_cells' atoms
   const StructInfo st = structs[sid[i]];
-  const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
-  const int64_t total = st.mode == kModeAllPairs
-                            ? st.count
-                            : st.count * (int64_t)((2 * st.reach[0] + 1) * (2 * st.reach[1] + 1) *
-                                                   (2 * st.reach[2] + 1));
-  // member test of candidate (j, image offset o)
-  auto member = [&](int64_t j, int o0, int o1, int o2, uint16_t& code) -> bool {
-    double Dx, Dy, Dz;
-    {
-#pragma clang fp contract(off)
-      Dx = pos[j] - xi;
-      Dy = pos[N + j] - yi;
-      Dz = pos[2 * N + j] - zi;
-    }
-    int n0, n1, n2;
-    min_image(st, Dx, Dy, Dz, n0, n1, n2);
-    n0 += o0;
-    n1 += o1;
-    n2 += o2;
-    if (j == i && n0 == 0 && n1 == 0 && n2 == 0) return false;
-    double dx, dy, dz;
-    image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
-    code = make_code(o0, o1, o2);
-    return norm2_exact(dx, dy, dz) < rc2;
-  };
-  // candidates c = G t + s of the sequence (the atoms of the structure, or the
-  // (atom, image) pairs with the image offsets innermost), G at a time; an
-  // accepted one's slot is the count so far plus the accepted lanes below it
-  const int R0 = st.reach[0], R1 = st.reach[1], R2 = st.reach[2];
-  const int w1 = 2 * R1 + 1, w2 = 2 * R2 + 1, nimg = (2 * R0 + 1) * w1 * w2;
-  const bool all_pairs = st.mode == kModeAllPairs;
   const int lane = threadIdx.x & 63;
-  const uint64_t gmask = ((1ull << G) - 1) << (lane & ~(G - 1));
-  const uint64_t below = (1ull << lane) - 1;
-  int32_t count = 0;
-  for (int64_t c0 = 0; c0 < total; c0 += G) {
-    const int64_t c = c0 + sub;
-    bool take = false;
-    uint16_t code = kCodeCenter;
-    int64_t j = 0;
-    if (c < total) {
-      int o0 = 0, o1 = 0, o2 = 0;
-      if (all_pairs) {
-        j = st.start + c;
-      } else {
-        const int64_t jl = c / nimg;
-        const int img = (int)(c - jl * nimg);
-        j = st.start + jl;
-        o0 = img / (w1 * w2) - R0;
-        o1 = (img / w2) % w1 - R1;
-        o2 = img % w2 - R2;
+  const uint64_t gmask = (G == 64 ? ~0ull : (1ull << (G & 63)) - 1) << (lane & ~(G - 1));
+  int32_t* lj = list_j[threadIdx.x / G];
+  uint16_t* lc = list_c[threadIdx.x / G];
+  const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
+  const bool images = st.mode == kModeImages;
+  RowSink<EXACT> sink{V, L, N, i, images};
+  double bound[3] = {0.0, 0.0, 0.0};  // r_c / w_k, slightly enlarged
+  if (images)
+    for (int k = 0; k < 3; ++k)
+      bound[k] = sqrt(rcR2 * (st.Hi[k] * st.Hi[k] + st.Hi[3 + k] * st.Hi[3 + k] + st.Hi[6 + k] * st.Hi[6 + k])) *
+                     (1.0 + 1e-9) + 1e-9;
+  int listed = 0;
+  auto exact_pass = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int q0 = 0; q0 < listed; q0 += G) {
+      const int q = q0 + sub;
+      bool ta = false, to = false;
+      int32_t j = 0;
+      uint16_t code = kCodeCenter;
+      if (q < listed) {
+        j = lj[q];
+        code = lc[q];
+        double Dx, Dy, Dz;
+        {
+#pragma clang fp contract(off)
+          Dx = pos[j] - xi;
+          Dy = pos[N + j] - yi;
+          Dz = pos[2 * N + j] - zi;
+        }
+        int n0, n1, n2, oa, ob, oc;
+        min_image(st, Dx, Dy, Dz, n0, n1, n2);
+        split_code(code, oa, ob, oc);
+        n0 += oa;
+        n1 += ob;
+        n2 += oc;
+        if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
+          double dx, dy, dz;
+          image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
+          const double r2 = norm2_exact(dx, dy, dz);
+          ta = EXACT && r2 < rcA2;
+          to = !ta && r2 < rcR2;
+        }
       }
-      take = member(j, o0, o1, o2, code);
+      const uint64_t ma = __ballot(ta) & gmask, mo = __ballot(to) & gmask;
+      if (ta) sink.put(true, sink.na + lanes_below(ma), j, code);
+      if (to) sink.put(false, sink.no + lanes_below(mo), j, code);
+      sink.na += __popcll(ma);
+      sink.no += __popcll(mo);
     }
-    const uint64_t mt = __ballot(take) & gmask;
-    if (take) {
-      const int32_t p = count + __popcll(mt & below);
-      if (p < V.MR) {
-        V.nlR[(int64_t)p * N + i] = (int32_t)j;
-        V.cdR[(int64_t)p * N + i] = code;
+    listed = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  for (int64_t j0 = 0; j0 < st.count; j0 += G) {
+    const bool have = j0 + sub < st.count;
+    const int64_t j = st.start + min(j0 + sub, st.count - 1);
+    int from[3] = {0, 0, 0}, n[3] = {1, 1, 1};
+    if (images) {
+      const double Dx = pos[j] - xi, Dy = pos[N + j] - yi, Dz = pos[2 * N + j] - zi;
+      int n0, n1, n2;
+      min_image(st, Dx, Dy, Dz, n0, n1, n2);
+      const double s[3] = {Dx * st.Hi[0] + Dy * st.Hi[3] + Dz * st.Hi[6] + n0,
+                           Dx * st.Hi[1] + Dy * st.Hi[4] + Dz * st.Hi[7] + n1,
+                           Dx * st.Hi[2] + Dy * st.Hi[5] + Dz * st.Hi[8] + n2};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {  // (fmax and fmin keep the range for a NaN)
+        from[k] = (int)fmax((double)-st.reach[k], ceil(-bound[k] - s[k]));
+        n[k] = max((int)fmin((double)st.reach[k], floor(bound[k] - s[k])) - from[k] + 1, 0);
       }
     }
-    count += __popcll(mt);
+    const int c = have ? n[0] * n[1] * n[2] : 0;
+    int32_t upto = c;  // pairs of the lanes up to this one
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const int32_t v = __shfl_up(upto, off, G);
+      if (sub >= off) upto += v;
+    }
+    const int32_t all = __shfl(upto, G - 1, G);
+    // list them, kWideList at most at a time
+    for (int32_t first = 0; first < all;) {
+      const int32_t room = min(kWideList - listed, all - first);
+      for (int32_t q = max(upto - c, first); q < min(upto, first + room); ++q) {
+        const int o = q - (upto - c), o2 = o % n[2], o1 = o / n[2] % n[1], o0 = o / (n[1] * n[2]);
+        lj[listed + q - first] = (int32_t)j;
+        lc[listed + q - first] = make_code(from[0] + o0, from[1] + o1, from[2] + o2);
+      }
+      listed += room;
+      first += room;
+      if (listed == kWideList) exact_pass();
+    }
   }
-  if (sub == 0) {
-    V.nnR[i] = count;
-    if (count > V.MR) atomicMax(overflow, count);
-  }
+  if (listed) exact_pass();
+  sink.template finish<G>(sub, overflow);
 }
 
 // rev[m][i] = position of (i, -offset) in the row of j = nl[m][i] (rows
@@ -494,6 +703,140 @@ __global__ void k_reverse(int64_t N, const int32_t* __restrict__ nn, const int32
     }
   }
   if (bad) atomicExch(err, 1);
+}
+
+// Reverse index of exact rows built without candidates: rev[m][i] = position
+// of (i, -image) in the row of j, searched in the part of that row (angular
+// or other) the entry belongs to -- membership of a pair is the same bits seen
+// from either atom -- and with it the invariants of k_check_rows: counts, the
+// neighbour inside the structure, the entry found pointing back with the
+// opposite image code, codes within the image reach (*bad, the same bits).
+// G lanes per atom; a lane's searches advance together, kReverseChunk at a
+// time.  For a batch (DISP) it also writes every entry's displacement and
+// species.
+template <bool DISP, int G>
+__global__ void __launch_bounds__(kBlock) k_reverse_exact(
+    int64_t N, Lists L, const double* __restrict__ pos, const int32_t* __restrict__ types,
+    const int32_t* __restrict__ sid, const StructInfo* __restrict__ structs, float4* __restrict__ disp,
+    int32_t* __restrict__ err, int32_t* __restrict__ bad) {
+  constexpr int U = kReverseChunk;
+  const int sub = threadIdx.x & (G - 1);
+  const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
+  if (i >= N) return;
+  const int32_t* __restrict__ nl = L.nlR;
+  const uint16_t* __restrict__ cd = L.cdR;
+  const int nn = L.nnR[i], na = L.nnA[i];
+  if (nn > L.MR) return;  // overflow: reported by the builder
+  const StructInfo& st = structs[sid[i]];
+  const bool images = st.mode == kModeImages;
+  const int64_t s_lo = st.start, s_hi = st.start + st.count;
+  int32_t b = na < 0 || nn < 0 || na > nn ? 1 : 0;
+  bool lost = false;
+  double xi = 0.0, yi = 0.0, zi = 0.0;
+  if (DISP) {
+    xi = pos[i];
+    yi = pos[N + i];
+    zi = pos[2 * N + i];
+  }
+  for (int m0 = sub; m0 < nn; m0 += U * G) {
+    int32_t j[U];
+    uint16_t code[U];
+    uint32_t key[U];
+    int lo[U], hi[U], found[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + u * G;
+      const int64_t e = m < nn ? (int64_t)m * N + i : i;
+      j[u] = nl[e];
+      code[u] = images ? cd[e] : kCodeCenter;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + u * G;
+      lo[u] = 0;
+      hi[u] = -1;  // an empty search for entries past the row
+      found[u] = -1;
+      int oa, ob, oc;
+      split_code(code[u], oa, ob, oc);
+      key[u] = (uint32_t)make_code(-oa, -ob, -oc);
+      if (m >= nn) continue;
+      if (j[u] < s_lo || j[u] >= s_hi) {
+        b |= 2;
+        j[u] = (int32_t)i;
+        continue;
+      }
+      if (images && (abs(oa) > st.reach[0] || abs(ob) > st.reach[1] || abs(oc) > st.reach[2])) b |= 16;
+      const int nj = min(L.nnR[j[u]], L.MR), aj = min(L.nnA[j[u]], nj);
+      lo[u] = m < na ? 0 : aj;
+      hi[u] = (m < na ? aj : nj) - 1;
+    }
+    double px[U], py[U], pz[U];
+    int32_t tj[U];
+    if constexpr (DISP) {  // on their way during the searches
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int32_t q = m0 + u * G < nn ? j[u] : (int32_t)i;
+        px[u] = pos[q];
+        py[u] = pos[N + q];
+        pz[u] = pos[2 * N + q];
+        tj[u] = types[q];
+      }
+    }
+    for (;;) {
+      bool any = false;
+      int mid[U];
+      int32_t jj[U];
+      uint32_t kk[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool open = found[u] < 0 && lo[u] <= hi[u];
+        any |= open;
+        mid[u] = open ? (lo[u] + hi[u]) >> 1 : -1;
+        jj[u] = 0;
+        kk[u] = key[u];
+        if (open) {
+          jj[u] = nl[(int64_t)mid[u] * N + j[u]];
+          if (images) kk[u] = cd[(int64_t)mid[u] * N + j[u]];
+        }
+      }
+      if (!any) break;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (mid[u] < 0) continue;
+        if (jj[u] == (int32_t)i && kk[u] == key[u]) found[u] = mid[u];
+        else if (jj[u] < (int32_t)i || (jj[u] == (int32_t)i && kk[u] < key[u])) lo[u] = mid[u] + 1;
+        else hi[u] = mid[u] - 1;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + u * G;
+      if (m >= nn) continue;
+      const int64_t e = (int64_t)m * N + i;
+      if (found[u] < 0) {
+        lost = true;
+        found[u] = 0;
+      }
+      L.revR[e] = found[u];
+      if constexpr (DISP) {
+        double Dx, Dy, Dz;
+        {
+#pragma clang fp contract(off)
+          Dx = px[u] - xi;
+          Dy = py[u] - yi;
+          Dz = pz[u] - zi;
+        }
+        int n0, n1, n2, oa, ob, oc;
+        min_image(st, Dx, Dy, Dz, n0, n1, n2);
+        split_code(code[u], oa, ob, oc);
+        double dx, dy, dz;
+        image_disp(st, Dx, Dy, Dz, n0 + oa, n1 + ob, n2 + oc, dx, dy, dz);
+        disp[e] = make_float4((float)dx, (float)dy, (float)dz, __int_as_float(tj[u]));
+      }
+    }
+  }
+  if (lost) atomicExch(err, 1);
+  if (b) atomicOr(bad, b);
 }
 
 // ---- row order for the network pass: atoms grouped by species in
@@ -587,10 +930,11 @@ void launch_order_atoms(const BuildArgs& b, hipStream_t s) {
                      b.structs, b.key, b.cell_count, g);
   hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, b.cell_count, b.cell_start,
                      b.n_cells, g);
-  hipLaunchKernelGGL(k_cell_scatter, grid_for(b.N), dim3(kBlock), 0, s, b.key, b.N,
+  hipLaunchKernelGGL(k_cell_scatter, grid_for(b.N), dim3(kBlock), 0, s, b.key, b.N, b.sid_ext, b.structs,
                      b.cell_start, b.cell_fill, b.perm, g);
-  hipLaunchKernelGGL(k_cell_sort, dim3(div_up(b.n_cells, kBlock / 64)), dim3(kBlock), 0, s, b.cell_start,
-                     b.cell_count, b.n_cells, b.ext_src, b.perm, g);
+  if (b.cell_rows)
+    hipLaunchKernelGGL(k_cell_sort, dim3(div_up(b.n_cells, kBlock / 64)), dim3(kBlock), 0, s, b.cell_start,
+                       b.cell_count, b.cell_fill, b.n_cells, b.ext_src, b.perm, g);
   hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
 }
 
@@ -602,12 +946,54 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
                      pos, vel, types, ext, pos_ref, gate, mu_cum, count);
 }
 
-void launch_build_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                       const Lists& L, hipStream_t s) {
-  BuildArgs bv = b;
-  bv.gate = nullptr;
-  launch_build_verlet(bv, V, s);
-  launch_filter_rows(b, st0, batch, V, L, s);
+// Below this many atoms the row kernels give an atom more lanes: a whole wave
+// in the builders (by cells 14 us against 17 with sixteen lanes for 3,995
+// atoms, 24 against 34 for ten cells of 100 to 1,000; at 131,072 atoms the
+// wave per atom takes 185 us against 136), sixteen lanes in the reverse
+// search: each lane then has one or two steps, where the chip is not full
+// anyway.
+constexpr int64_t kFewAtoms = 16384;
+
+// blocks along y share a cell's atoms: enough for cells of half as many again
+// as the average (fuller ones take another turn)
+template <bool EXACT, int G>
+static void launch_cells(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s) {
+  const int64_t per = b.N * 3 / (2 * (int64_t)b.n_cells) + 1;
+  const int64_t y = std::min<int64_t>(div_up(per, kBlock / G), 64);
+  hipLaunchKernelGGL((k_build_rows_cells<EXACT, G>), dim3((unsigned)b.n_cells, (unsigned)y), dim3(kBlock), 0, s, b.pos,
+                     b.N, b.structs, b.n_struct, b.cell_start, b.cell_count, b.n_cells, b.rcR2, b.rcA2, V, L,
+                     b.overflow, b.gate);
+}
+
+template <bool EXACT>
+static void launch_members(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s) {
+  if (b.cell_rows) {
+    if (b.N < kFewAtoms) launch_cells<EXACT, 64>(b, V, L, s);
+    else launch_cells<EXACT, 16>(b, V, L, s);
+  }
+  if (b.wide_rows) {
+    if (b.N < kFewAtoms)
+      hipLaunchKernelGGL((k_build_rows_wide<EXACT, 64>), grid_for(b.N * 64), dim3(kBlock), 0, s, b.pos, b.N, b.sid,
+                         b.structs, b.rcR2, b.rcA2, V, L, b.overflow, b.gate);
+    else
+      hipLaunchKernelGGL((k_build_rows_wide<EXACT, 16>), grid_for(b.N * 16), dim3(kBlock), 0, s, b.pos, b.N, b.sid,
+                         b.structs, b.rcR2, b.rcA2, V, L, b.overflow, b.gate);
+  }
+}
+
+template <bool DISP, int G>
+static void launch_reverse_exact(const BuildArgs& b, const Lists& L, hipStream_t s) {
+  hipLaunchKernelGGL((k_reverse_exact<DISP, G>), grid_for(b.N * G), dim3(kBlock), 0, s, b.N, L, b.pos, b.types, b.sid,
+                     b.structs, b.disp, b.overflow + 2, b.overflow + 6);
+}
+
+void launch_build_rows(const BuildArgs& b0, const Lists& V, const Lists& L, hipStream_t s) {
+  BuildArgs b = b0;
+  b.gate = nullptr;
+  launch_members<true>(b, V, L, s);
+  const bool wide = b.N < kFewAtoms;
+  if (b.disp) wide ? launch_reverse_exact<true, 16>(b, L, s) : launch_reverse_exact<true, 4>(b, L, s);
+  else wide ? launch_reverse_exact<false, 16>(b, L, s) : launch_reverse_exact<false, 4>(b, L, s);
 }
 
 void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate, hipStream_t s) {
@@ -618,12 +1004,7 @@ void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate
 // Candidate rows at sqrt(b.rcR2) and their reverse index, rebuilt when the
 // gate is set.
 void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s) {
-  // structures without cells take their rows from the wide kernel
-  hipLaunchKernelGGL(k_build_rows, grid_for(b.N * kCellLanes), dim3(kBlock), 0, s, b.pos, b.N, b.sid,
-                     b.structs, b.cell_start, b.cell_count, b.rcR2, V, b.overflow + 5, b.gate);
-  if (b.wide_rows)
-    hipLaunchKernelGGL(k_build_rows_wide, grid_for(b.N * kBuildLanes), dim3(kBlock), 0, s, b.pos, b.N,
-                       b.sid, b.structs, b.rcR2, V, b.overflow + 5, b.gate);
+  launch_members<false>(b, V, V, s);
   launch_reverse(b.N, V, b.overflow + 2, b.gate, s);
 }
 

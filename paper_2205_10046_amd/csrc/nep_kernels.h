@@ -26,6 +26,8 @@ struct BuildArgs {
   const int32_t* gate;        // rebuild kernels run only when *gate != 0 (NULL: always)
   float4* disp = nullptr;     // batches: displacement and species of every exact entry, [MR][N]
   int32_t wide_rows = 0;      // some structure has no cells: its rows come from k_build_rows_wide
+  int32_t cell_rows = 0;      // some structure has cells: its rows come from k_build_rows_cells
+  int32_t n_struct = 1;
   // optional: velocities and caller indices permuted with the positions
   const double* vel_src = nullptr;
   double* vel_dst = nullptr;
@@ -69,9 +71,9 @@ void launch_fill_i32(int32_t* a, int64_t n, int32_t v, hipStream_t s);
 void launch_assign_struct(const int64_t* offs, int32_t n_struct, int64_t N, int32_t* sid,
                           hipStream_t s);
 void launch_order_atoms(const BuildArgs& b, hipStream_t s);
-// Exact rows at the cutoffs of b from candidate rows V at sqrt(b.rcR2).
-void launch_build_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                       const Lists& L, hipStream_t s);
+// Exact rows L at the cutoffs of b with their reverse index, every row
+// invariant checked (flags [2] and [6]); V's rows serve as scratch.
+void launch_build_rows(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s);
 void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate, hipStream_t s);
 // Sets bits of *bad when the exact rows break an invariant the evaluation
 // kernels rely on for in-bounds access (see neighbor.hip).
