@@ -449,7 +449,7 @@ int nep_get_timing(const nep_handle *h, int32_t max, const char **names,
  * structure, chosen by the number of atoms; 1: the batched path, fixed by the
  * handle's first batch): out[7] = {descriptor radial functions per walk,
  * block, quads of lanes per atom; the same three of the partial forces;
- * gather lanes per atom}.  Zeros before the first evaluation of that kind.  Not
+ * quads of lanes per atom of the gather}.  Zeros before the first evaluation of that kind.  Not
  * from the paper: it names the variants that profiles refer to. */
 int nep_get_tuning(const nep_handle *h, int32_t batch, int32_t out[7]);
 

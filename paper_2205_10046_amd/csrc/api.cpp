@@ -316,8 +316,7 @@ struct ModelTables {
 // Kernel shape of one kind of call (single structure, batch), see pick_shape().
 struct Tuning {
   bool done = false;
-  int quads = 1;          // quads of lanes per atom of the pair kernels
-  int lanes_gather = 4;   // lanes per atom of the force gather
+  int quads = 1;          // quads of lanes per atom of the pair kernels and the gather
 };
 
 }  // namespace
@@ -1009,7 +1008,6 @@ void forces(nep_handle* h, const Prepared& pp, hipStream_t s, const DevModel* mo
   }
   {
     Stage st(h, "gather", s);
-    a.lanes = t.lanes_gather;
     if (kick) {  // the second half kick of a velocity-Verlet step
       a.kick_vel = kick->vel;
       a.kick_inv_mass = kick->inv_mass;
@@ -2816,7 +2814,7 @@ int nep_get_tuning(const nep_handle* h, int32_t batch, int32_t out[7]) {
   if (!h || !out || (batch != 0 && batch != 1))
     return fail(nullptr, {NEP_E_INVALID_ARG, "handle, batch in {0, 1} and out[7] are required"});
   const Tuning& t = h->tune[batch];
-  const int32_t v[7] = {h->M.nA, kBlock, t.quads, h->M.nA, kBlock, t.quads, t.lanes_gather};
+  const int32_t v[7] = {h->M.nA, kBlock, t.quads, h->M.nA, kBlock, t.quads, t.quads};
   for (int k = 0; k < 7; ++k) out[k] = t.done ? v[k] : 0;
   return NEP_OK;
 }

@@ -950,8 +950,10 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
 // in the builders (by cells 14 us against 17 with sixteen lanes for 3,995
 // atoms, 24 against 34 for ten cells of 100 to 1,000; at 131,072 atoms the
 // wave per atom takes 185 us against 136), sixteen lanes in the reverse
-// search: each lane then has one or two steps, where the chip is not full
-// anyway.
+// searches and the filter: each lane then has one or two steps, where the chip
+// is not full anyway.  Rows of the 4-species alloy, few lanes against many, in
+// us: 46 : 25 at 4,000 atoms, 50 : 43 at 10,976, 65 : 62 at 19,652, 78 : 89 at
+// 32,000.
 constexpr int64_t kFewAtoms = 16384;
 
 // blocks along y share a cell's atoms: enough for cells of half as many again
@@ -1011,9 +1013,12 @@ void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s) {
 // Exact radial row from the candidate row with the same float64 membership
 // test: the entries with |d|^2 < (r_c^A)^2 first, then the others, each part
 // in candidate order; nnA = size of the first part.  V.fmap[m][i] = exact
-// position of candidate m (or -1).  kFilterLanes lanes per atom take the
-// candidates m = s, s + 4, ..., so the 16 atoms of a wave read and write
-// whole 64-byte runs of a row.  Both passes walk a lane's candidates in
+// position of candidate m (or -1).  G lanes per atom take the candidates m =
+// s, s + G, ...: with four the 16 atoms of a wave read and write whole
+// 64-byte runs of a row, and with many atoms the loads are what the kernel
+// takes (its address units are busy for three quarters of it; 117 us for 131,072
+// atoms); with few it is a chain of steps, shorter with sixteen lanes (18 us
+// to 8.5 for 2,048 atoms).  Both passes walk a lane's candidates in
 // chunks of kFilterChunk: the index words of a chunk are loaded together,
 // then the positions (pass 1) or the row words (pass 2), so a lane has a
 // chunk's loads in flight at once instead of one dependent chain per
@@ -1021,17 +1026,16 @@ void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s) {
 // register bit masks; pass 2 goes through the candidates in order, and
 // counts over wave ballots of the class flags give each member its exact position.
 // The rows are the same as those of a single sequential pass.
-constexpr int kFilterLanes = 4;
 constexpr int kFilterChunk = 4;
 
-template <bool BATCH>
+template <bool BATCH, int G>
 __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict__ pos, int64_t N,
                                                         const int32_t* __restrict__ sid,
                                                         const StructInfo* __restrict__ structs,
                                                         StructInfo st0, Lists V, double rcR2,
                                                         double rcA2, Lists L,
                                                         int32_t* __restrict__ overflow) {
-  constexpr int G = kFilterLanes, U = kFilterChunk;
+  constexpr int U = kFilterChunk;
   constexpr int32_t kOuter = -2, kAngular = -3;
   const int sub = threadIdx.x & (G - 1);
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
@@ -1050,7 +1054,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
   const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
   int32_t na = 0, no = 0;
   // classes of the lane's first 64 candidates (t = local index) as bit masks;
-  // later ones (rows over 256 candidates) go through V.fmap
+  // later ones (rows over 64 G candidates) go through V.fmap
   uint64_t mask_a = 0, mask_o = 0;
   // the index words of chunk t0 + U are loaded while chunk t0's positions
   // are in flight
@@ -1204,20 +1208,18 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
 
 // rev of the exact rows: the filter left in L.revR[p][i] the candidate
 // position of i in the row of j = L.nlR[p][i]; the exact position there is
-// V.fmap of that candidate entry, written in place.  kRevLanes lanes per atom
-// take exact entries p = s, s + 4, ..., so a wave writes whole 64-byte runs of
-// a row; a lane loads the words of kFilterChunk entries, then their map
+// V.fmap of that candidate entry, written in place.  G lanes per atom
+// take exact entries p = s, s + G, ..., four or sixteen as in the filter (2,048
+// atoms: 6.6 us with four lanes, 4.1 with sixteen); a lane loads the words of kFilterChunk entries, then their map
 // entries, then writes them.  For a batch (DISP) it also writes every
 // entry's float32 displacement and species (as bits), read by each parameter
 // set's passes.
-constexpr int kRevLanes = 4;
-
-template <bool DISP>
+template <bool DISP, int G>
 __global__ void __launch_bounds__(kBlock) k_reverse_from_candidates(
     int64_t N, Lists V, Lists L, const double* __restrict__ pos, const int32_t* __restrict__ types,
     const int32_t* __restrict__ sid, const StructInfo* __restrict__ structs, float4* __restrict__ disp,
     int32_t* __restrict__ err) {
-  constexpr int G = kRevLanes, U = kFilterChunk;
+  constexpr int U = kFilterChunk;
   const int sub = threadIdx.x & (G - 1);
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
   if (i >= N) return;
@@ -1385,22 +1387,29 @@ void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs,
                      (int32_t)(batch ? 1 : 0), L, bad);
 }
 
-void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                        const Lists& L, hipStream_t s) {
-  const dim3 grid = grid_for(b.N * kFilterLanes);
+template <int G>
+static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V, const Lists& L,
+                            hipStream_t s) {
+  const dim3 grid = grid_for(b.N * G);
   if (batch)
-    hipLaunchKernelGGL(k_filter_rows<true>, grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
+    hipLaunchKernelGGL((k_filter_rows<true, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
                        st0, V, b.rcR2, b.rcA2, L, b.overflow);
   else
-    hipLaunchKernelGGL(k_filter_rows<false>, grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
+    hipLaunchKernelGGL((k_filter_rows<false, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
                        st0, V, b.rcR2, b.rcA2, L, b.overflow);
   if (b.disp)
-    hipLaunchKernelGGL((k_reverse_from_candidates<true>), grid_for(b.N * kRevLanes), dim3(kBlock), 0, s, b.N, V, L,
+    hipLaunchKernelGGL((k_reverse_from_candidates<true, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        b.pos, b.types, b.sid, b.structs, b.disp, b.overflow + 2);
   else
-    hipLaunchKernelGGL((k_reverse_from_candidates<false>), grid_for(b.N * kRevLanes), dim3(kBlock), 0, s, b.N, V, L,
+    hipLaunchKernelGGL((k_reverse_from_candidates<false, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        (const double*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr,
                        (const StructInfo*)nullptr, (float4*)nullptr, b.overflow + 2);
+}
+
+void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
+                        const Lists& L, hipStream_t s) {
+  if (b.N < kFewAtoms) launch_filter_g<16>(b, st0, batch, V, L, s);
+  else launch_filter_g<4>(b, st0, batch, V, L, s);
 }
 
 // flag = any atom whose displacement since the last build, plus horizon

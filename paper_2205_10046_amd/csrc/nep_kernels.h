@@ -59,8 +59,7 @@ struct EvalArgs {
   double kick_dt;
   const int32_t* rows;        // network row order, [rows_len]
   int64_t rows_len;
-  int32_t quads;              // quads of lanes per atom of the pair kernels (1 or 4)
-  int32_t lanes;              // lanes per atom of the gather (1 or 4)
+  int32_t quads;              // quads of lanes per atom of the pair kernels and the gather (1 or 4)
   int32_t mlp_bf16;
   int32_t batch;              // several structures: geometry from structs[sid]
   StructInfo st0;             // the geometry when batch == 0
