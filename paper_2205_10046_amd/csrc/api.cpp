@@ -373,7 +373,7 @@ struct nep_handle {
   int32_t *types_ext = nullptr, *types = nullptr, *types2 = nullptr, *sid_ext = nullptr, *sid = nullptr;
   int32_t *key = nullptr, *perm = nullptr, *ext_id = nullptr, *ext_id2 = nullptr, *inv = nullptr;
   int32_t *cell_count = nullptr, *cell_fill = nullptr, *cell_start = nullptr;
-  int32_t *rows = nullptr, *tblk = nullptr, *tex = nullptr, *toff = nullptr, *flags = nullptr;
+  int32_t *rows = nullptr, *tblk = nullptr, *tex = nullptr, *flags = nullptr;
   StructInfo* structs = nullptr;
   Lists L{};
   Lists V{};                       // candidate rows at r_c^R + skin (MD with a skin)
@@ -466,7 +466,7 @@ struct nep_handle {
     dev_free(types_ext); dev_free(types); dev_free(types2); dev_free(sid_ext); dev_free(sid);
     dev_free(key); dev_free(perm); dev_free(ext_id); dev_free(ext_id2); dev_free(inv);
     dev_free(cell_count); dev_free(cell_fill); dev_free(cell_start);
-    dev_free(rows); dev_free(tblk); dev_free(tex); dev_free(toff); dev_free(flags);
+    dev_free(rows); dev_free(tblk); dev_free(tex); dev_free(flags);
     dev_free(structs); dev_free(offs);
     cap_struct = 0;
     free_lists();
@@ -744,7 +744,7 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     h->rows_cap = rows_length(c, M.T);
     dev_alloc(h->rows, h->rows_cap);
     dev_alloc(h->tblk, kMaxTypes * type_row_blocks(c)); dev_alloc(h->tex, kMaxTypes * type_row_blocks(c));
-    dev_alloc(h->toff, kMaxTypes + 1); dev_alloc(h->flags, kNumFlags);
+    dev_alloc(h->flags, kNumFlags);
     HIPCHK(hipMemset(h->flags, 0, kNumFlags * sizeof(int32_t)));
     h->cap_part = num_partials(c);
     dev_alloc(h->partial, 11 * h->cap_part); dev_alloc(h->totals, 16);
@@ -798,6 +798,8 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.overflow = h->flags;
   b.disp = pp.batch ? h->disp : nullptr;
   b.n_struct = (int32_t)pp.sts.size();
+  b.n_types = h->M.T;
+  b.per_type = h->hp.nn_per_type;
   for (const StructInfo& st : pp.sts) (st.mode == kModeCells ? b.cell_rows : b.wide_rows) = 1;
   return b;
 }
@@ -873,7 +875,6 @@ Prepared prepare_batch(nep_handle* h, int32_t S, const int64_t* offs, const doub
     static_assert(sizeof(StructInfo) <= 256, "staging slot");
     std::memcpy(h->pinned, &pp.sts[0], sizeof(StructInfo));
     HIPCHK(hipMemcpyAsync(h->structs, h->pinned, sizeof(StructInfo), hipMemcpyHostToDevice, s));
-    launch_fill_i32(h->sid_ext, N, 0, s);
   } else {
     // the structure table and offsets go up from pinned staging in stream order
     const size_t nb = (size_t)S * sizeof(StructInfo), need = nb + (size_t)(S + 1) * sizeof(int64_t);
@@ -914,17 +915,20 @@ void check_row_flag(int32_t bits) {
                                  std::to_string(bits) + ")"};
 }
 
-// Rows for the current internal positions; grows the capacities (auto mode)
-// or fails (fixed capacities) when a row overflows.  Synchronises once.
-void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, hipStream_t s,
-                        bool check_types) {
+// The network's row order with the order of the atoms.
+void with_type_rows(nep_handle* h, BuildArgs& b) {
+  b.tblk = h->tblk;
+  b.tex = h->tex;
+  b.rows = h->rows;
+  b.rows_len = rows_length(b.N, h->M.T);
+}
+
+// Rows for the current internal positions, after launch_order_atoms cleared and
+// set the flags; grows the capacities (auto mode) or fails (fixed
+// capacities) when a row overflows.  Synchronises once.
+void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, hipStream_t s) {
   for (int attempt = 0; attempt < 3; ++attempt) {
-    launch_fill_i32(h->flags, 8, 0, s);
-    if (check_types) {
-      // flags[3]: species out of range, flags[4]: non-finite position
-      launch_check_types(h->types, pp.N, h->M.T, h->flags + 3, s);
-      launch_check_finite(h->pos, 3 * pp.N, h->flags + 4, s);
-    }
+    if (attempt) launch_fill_i32(h->flags, 8, 0, s);
     {
       Stage st(h, "neighbor_rows", s);
       launch_build_rows(b, h->V, h->L, s);
@@ -957,15 +961,15 @@ void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, h
 }
 
 void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, const int32_t* types_src,
-                     hipStream_t s, bool check) {
+                     hipStream_t s) {
   BuildArgs b = build_args(h, pp, pos_src, types_src, h->pos, h->types);
+  b.check = h->flags;
+  with_type_rows(h, b);
   {
     Stage st(h, "order_atoms", s);
     launch_order_atoms(b, s);
-    launch_type_rows(h->types, pp.N, h->M.T, h->hp.nn_per_type, h->tblk, h->tex, h->toff, h->rows,
-                     rows_length(pp.N, h->M.T), nullptr, s);
   }
-  build_rows_checked(h, pp, b, s, check);
+  build_rows_checked(h, pp, b, s);
 }
 
 // Kernel shape of a call.  A quad of lanes per atom uses the lanes best (a row
@@ -1049,7 +1053,7 @@ int compute_impl(nep_handle* h, int64_t N, const double* d_pos, const int32_t* d
                  const int32_t* pbc, double* d_energy, double* d_force, double* d_virial, double* d_totals,
                  hipStream_t s) {
   Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
-  order_and_build(h, pp, d_pos, d_types, s, true);
+  order_and_build(h, pp, d_pos, d_types, s);
   forces(h, pp, s);
   EvalArgs a = eval_args(h, pp, h->M);
   {
@@ -1114,7 +1118,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     models.push_back(h->M);
   }
   if (!reuse) {
-    order_and_build(h, pp, d_pos, d_types, s, true);
+    order_and_build(h, pp, d_pos, d_types, s);
     h->batch_rows_ready = true;
     h->batch_S = S;
     h->batch_N = N;
@@ -1413,7 +1417,7 @@ void server_tick(nep_server* sv) {
   }
   launch_srv_kick_drift(N, b.pos, b.vel, b.F, b.hdm, b.dta, b.move, s);
   Prepared pp = prepare_batch(h, S, offs.data(), boxes.data(), pbcs.data(), h->hp.rc_radial, false, true, s);
-  order_and_build(h, pp, b.pos, b.types, s, true);
+  order_and_build(h, pp, b.pos, b.types, s);
   forces(h, pp, s);
   EvalArgs a = eval_args(h, pp, h->M);
   launch_scatter_outputs(a, h->perm, b.E, b.F, b.W, s);
@@ -1904,7 +1908,7 @@ int nep_neighbors(nep_handle* h, int64_t N, const double* pos, const double box[
     Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     launch_fill_i32(h->types_ext, N, 0, s);
-    order_and_build(h, pp, h->pos_ext, h->types_ext, s, true);
+    order_and_build(h, pp, h->pos_ext, h->types_ext, s);
     int32_t *d_count = nullptr, *d_nbr = nullptr, *d_shift = nullptr;
     dev_alloc(d_count, N);
     dev_alloc(d_nbr, (size_t)N * cap);
@@ -2016,7 +2020,7 @@ int nep_descriptors(nep_handle* h, int64_t N, const double* pos, const int32_t* 
     Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    order_and_build(h, pp, h->pos_ext, h->types_ext, s, true);
+    order_and_build(h, pp, h->pos_ext, h->types_ext, s);
     EvalArgs a = eval_args(h, pp, h->M);
     a.quads = pick_shape(h, pp).quads;
     if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
@@ -2047,7 +2051,7 @@ int nep_latent(nep_handle* h, int64_t N, const double* pos, const int32_t* types
     Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    order_and_build(h, pp, h->pos_ext, h->types_ext, s, true);
+    order_and_build(h, pp, h->pos_ext, h->types_ext, s);
     const int NN = h->hp.n_neurons;
     dev_alloc(d_lat, (size_t)N * NN);
     dev_alloc(d_out, (size_t)N * NN);
@@ -2084,6 +2088,7 @@ void skin_rebuild(nep_handle* h, const Prepared& pp, double rl, const int32_t* g
   br.vel_dst = h->vel2;
   br.ext_in = h->ext_id;
   br.ext_out = h->ext_id2;
+  with_type_rows(h, br);
   launch_order_atoms(br, s);
   launch_commit_rebuild(N, h->pos2, h->vel2, h->types2, h->ext_id2, h->pos, h->vel, h->types,
                         h->ext_id, h->pos_ref, gate, s, mu_cum, h->flags + kFlagRebuilds);
@@ -2091,8 +2096,6 @@ void skin_rebuild(nep_handle* h, const Prepared& pp, double rl, const int32_t* g
   bv.rcR2 = rl * rl;
   bv.gate = gate;
   launch_build_verlet(bv, h->V, s);
-  launch_type_rows(h->types, N, h->M.T, h->hp.nn_per_type, h->tblk, h->tex, h->toff, h->rows,
-                   rows_length(N, h->M.T), gate, s);
 }
 
 void skin_filter(nep_handle* h, const Prepared& pp, hipStream_t s) {
@@ -2219,12 +2222,10 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
   // initial order from the caller arrays
   if (!cont) {
     BuildArgs b0 = build_args(h, pp, d_pos, d_types, h->pos, h->types);
+    b0.check = h->flags;
     launch_order_atoms(b0, s);
     launch_permute_md(h->perm, N, d_pos, d_vel, h->pos2, h->vel, s);
     HIPCHK(hipMemcpyAsync(h->ext_id, h->perm, N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    launch_fill_i32(h->flags, 8, 0, s);
-    launch_check_types(h->types, N, h->M.T, h->flags + 3, s);
-    launch_check_finite(h->pos, 3 * N, h->flags + 4, s);
   }
   for (int attempt = 0; !cont; ++attempt) {
     launch_fill_i32(h->flags, 3, 0, s);
@@ -2577,7 +2578,7 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
     return md_skin(h, pp, d_pos, d_vel, d_types, dt, n_steps, thermo_every, thermo_out, thermo_on_host,
                    n_rows, s, use_ens ? &ep : nullptr, ens_state, box_out);
   // initial order: internal <- caller, velocities follow
-  order_and_build(h, pp, d_pos, d_types, s, true);
+  order_and_build(h, pp, d_pos, d_types, s);
   launch_permute_md(h->perm, N, d_pos, d_vel, h->pos2, h->vel, s);  // pos2 is scratch here
   HIPCHK(hipMemcpyAsync(h->ext_id, h->perm, N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
   forces(h, pp, s);
@@ -2612,10 +2613,9 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       b.ext_src = h->ext_id;
       {
         Stage st(h, "order_atoms", s);
+        with_type_rows(h, b);
         launch_order_atoms(b, s);
         launch_permute_md(h->perm, N, h->pos, h->vel, h->pos2, h->vel2, s);
-        launch_type_rows(h->types2, N, h->M.T, h->hp.nn_per_type, h->tblk, h->tex, h->toff, h->rows,
-                         rows_length(N, h->M.T), nullptr, s);
       }
       std::swap(h->pos, h->pos2);
       std::swap(h->vel, h->vel2);

@@ -224,17 +224,6 @@ void launch_check_finite(const double* a, int64_t n, int32_t* flag, hipStream_t 
     hipLaunchKernelGGL(k_check_finite, dim3(div_up(n, kBlock)), dim3(kBlock), 0, s, a, n, flag);
 }
 
-__global__ void k_check_types(const int32_t* __restrict__ t, int64_t n, int32_t T,
-                              int32_t* __restrict__ flag) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n && (t[k] < 0 || t[k] >= T)) atomicExch(flag, 1);
-}
-
-void launch_check_types(const int32_t* types, int64_t n, int32_t T, int32_t* flag, hipStream_t s) {
-  if (n > 0)
-    hipLaunchKernelGGL(k_check_types, dim3(div_up(n, kBlock)), dim3(kBlock), 0, s, types, n, T, flag);
-}
-
 // out[k] = in[src[k]]
 __global__ void k_gather_i32(const int32_t* __restrict__ src, int64_t N, const int32_t* __restrict__ in,
                              int32_t* __restrict__ out) {

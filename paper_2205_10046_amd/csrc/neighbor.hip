@@ -75,23 +75,29 @@ __device__ inline void cell_coords(const StructInfo& st, double x, double y, dou
   cz = c[2];
 }
 
-__global__ void k_cell_key(const double* __restrict__ pos, int64_t N,
-                           const int32_t* __restrict__ sid, const StructInfo* __restrict__ structs,
-                           int32_t* __restrict__ key, int32_t* __restrict__ cell_count,
-                           const int32_t* gate) {
+// Structure of source atom e, and its cell in one with cells.
+__device__ __forceinline__ int32_t struct_of(const BuildArgs& b, int64_t e) {
+  return b.n_struct == 1 ? 0 : b.sid_ext[e];
+}
+
+__device__ __forceinline__ int cell_of(const StructInfo& st, double x, double y, double z) {
+  int cx, cy, cz;
+  cell_coords(st, x, y, z, cx, cy, cz);
+  return st.cell_off + (cz * st.ncell[1] + cy) * st.ncell[0] + cx;
+}
+
+__global__ void k_cell_key(BuildArgs b) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= N || gated_off(gate)) return;
-  const StructInfo& st = structs[sid[e]];
+  if (e >= b.N || gated_off(b.gate)) return;
+  const StructInfo& st = b.structs[struct_of(b, e)];
   if (st.mode != kModeCells) {  // one cell, in caller order (k_cell_scatter)
-    key[e] = st.cell_off;
-    if (e == st.start) cell_count[st.cell_off] = (int32_t)st.count;
+    b.key[e] = st.cell_off;
+    if (e == st.start) b.cell_count[st.cell_off] = (int32_t)st.count;
     return;
   }
-  int cx, cy, cz;
-  cell_coords(st, pos[e], pos[N + e], pos[2 * N + e], cx, cy, cz);
-  const int k = st.cell_off + (cz * st.ncell[1] + cy) * st.ncell[0] + cx;
-  key[e] = k;
-  atomicAdd(&cell_count[k], 1);
+  const int k = cell_of(st, b.pos_ext[e], b.pos_ext[b.N + e], b.pos_ext[2 * b.N + e]);
+  b.key[e] = k;
+  atomicAdd(&b.cell_count[k], 1);
 }
 
 // Exclusive scan of n int32 counts by one block of 1024 threads.
@@ -124,20 +130,17 @@ __global__ void __launch_bounds__(1024) k_scan_1block(const int32_t* __restrict_
 // A structure without cells keeps its order: its atoms come in caller order
 // on the first call and stay so, and its cell needs no slots and no sort (its
 // cell_fill stays 0).
-__global__ void k_cell_scatter(const int32_t* __restrict__ key, int64_t N, const int32_t* __restrict__ sid,
-                               const StructInfo* __restrict__ structs, const int32_t* __restrict__ cell_start,
-                               int32_t* __restrict__ cell_fill, int32_t* __restrict__ perm,
-                               const int32_t* gate) {
+__global__ void k_cell_scatter(BuildArgs b) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= N || gated_off(gate)) return;
-  const StructInfo& st = structs[sid[e]];
-  int k = key[e];
+  if (e >= b.N || gated_off(b.gate)) return;
+  const StructInfo& st = b.structs[struct_of(b, e)];
+  int k = b.key[e];
   if (st.mode != kModeCells) {
-    perm[cell_start[k] + (e - st.start)] = (int32_t)e;
+    b.perm[b.cell_start[k] + (e - st.start)] = (int32_t)e;
     return;
   }
-  int slot = atomicAdd(&cell_fill[k], 1);
-  perm[cell_start[k] + slot] = (int32_t)e;
+  int slot = atomicAdd(&b.cell_fill[k], 1);
+  b.perm[b.cell_start[k] + slot] = (int32_t)e;
 }
 
 // Order the atoms of each cell by caller index (ext[source index], or the
@@ -208,21 +211,29 @@ __global__ void k_gather_atoms(BuildArgs b) {
   const int64_t N = b.N;
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= N || gated_off(b.gate)) return;
-  int64_t e = b.perm[k];
-  for (int c = 0; c < 3; ++c) b.pos[c * N + k] = b.pos_ext[c * N + e];
-  b.types[k] = b.types_ext[e];
-  b.sid[k] = b.sid_ext[e];
+  const int64_t e = b.perm[k];
+  const double x = b.pos_ext[e], y = b.pos_ext[N + e], z = b.pos_ext[2 * N + e];
+  const int32_t t = b.types_ext[e];
+  b.pos[k] = x;
+  b.pos[N + k] = y;
+  b.pos[2 * N + k] = z;
+  b.types[k] = t;
+  b.sid[k] = struct_of(b, e);
   if (b.vel_src)
     for (int c = 0; c < 3; ++c) b.vel_dst[c * N + k] = b.vel_src[c * N + e];
   if (b.ext_in) b.ext_out[k] = b.ext_in[e];
+  if (!b.check) return;
+  if (t < 0 || t >= b.n_types) atomicExch(&b.check[3], 1);
+  if (!(isfinite(x) && isfinite(y) && isfinite(z))) atomicExch(&b.check[4], 1);
 }
 
-__global__ void k_fill_cells(int32_t* __restrict__ a, int32_t* __restrict__ b, int64_t n,
-                             const int32_t* gate) {
+__global__ void k_fill_cells(BuildArgs b) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !gated_off(gate)) {
-    a[i] = 0;
-    b[i] = 0;
+  if (gated_off(b.gate)) return;
+  if (b.check && i < 8) b.check[i] = 0;
+  if (i < b.n_cells) {
+    b.cell_count[i] = 0;
+    b.cell_fill[i] = 0;
   }
 }
 
@@ -870,26 +881,22 @@ __global__ void __launch_bounds__(kBlock) k_type_block_count(const int32_t* __re
   if (t < Tn) tblk[(int64_t)t * nb + blockIdx.x] = hist[t];
 }
 
-// shift[t] = (padded start of species t) - (exclusive count before species t)
-__global__ void k_type_shift(const int32_t* __restrict__ tex, int64_t N, int32_t Tn, int32_t nb,
-                             int32_t* __restrict__ shift, const int32_t* gate) {
-  if (threadIdx.x != 0 || blockIdx.x != 0 || gated_off(gate)) return;
-  int32_t o = 0;
-  for (int t = 0; t < Tn; ++t) {
-    const int32_t first = tex[(int64_t)t * nb];
-    const int32_t next = t + 1 < Tn ? tex[(int64_t)(t + 1) * nb] : (int32_t)N;
-    shift[t] = o - first;
-    o += (next - first + kRowGroup - 1) / kRowGroup * kRowGroup;
-  }
-}
 
 __global__ void __launch_bounds__(kBlock) k_type_block_scatter(
     const int32_t* __restrict__ types, int64_t N, int32_t Tn, int32_t per_type, int32_t nb,
-    const int32_t* __restrict__ tex, const int32_t* __restrict__ shift, int32_t* __restrict__ rows,
-    const int32_t* gate) {
+    const int32_t* __restrict__ tex, int32_t* __restrict__ rows, const int32_t* gate) {
   constexpr int kWaves = kBlock / 64;
-  __shared__ int32_t wcount[kWaves][kMaxTypes];
+  __shared__ int32_t wcount[kWaves][kMaxTypes], shift[kMaxTypes];
   if (gated_off(gate)) return;
+  if (threadIdx.x == 0) {  // species t's rows start at a multiple of kRowGroup
+    int32_t o = 0;
+    for (int t = 0; t < Tn; ++t) {
+      const int32_t first = tex[(int64_t)t * nb];
+      const int32_t next = t + 1 < Tn ? tex[(int64_t)(t + 1) * nb] : (int32_t)N;
+      shift[t] = o - first;
+      o += (next - first + kRowGroup - 1) / kRowGroup * kRowGroup;
+    }
+  }
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t i = (int64_t)blockIdx.x * kBlock + t;
   const bool live = i < N;
@@ -920,22 +927,6 @@ void launch_fill_i32(int32_t* a, int64_t n, int32_t v, hipStream_t s) {
 void launch_assign_struct(const int64_t* offs, int32_t n_struct, int64_t N, int32_t* sid,
                           hipStream_t s) {
   hipLaunchKernelGGL(k_assign_struct, grid_for(N), dim3(kBlock), 0, s, offs, n_struct, N, sid);
-}
-
-void launch_order_atoms(const BuildArgs& b, hipStream_t s) {
-  const int32_t* g = b.gate;
-  hipLaunchKernelGGL(k_fill_cells, grid_for(b.n_cells), dim3(kBlock), 0, s, b.cell_count,
-                     b.cell_fill, (int64_t)b.n_cells, g);
-  hipLaunchKernelGGL(k_cell_key, grid_for(b.N), dim3(kBlock), 0, s, b.pos_ext, b.N, b.sid_ext,
-                     b.structs, b.key, b.cell_count, g);
-  hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, b.cell_count, b.cell_start,
-                     b.n_cells, g);
-  hipLaunchKernelGGL(k_cell_scatter, grid_for(b.N), dim3(kBlock), 0, s, b.key, b.N, b.sid_ext, b.structs,
-                     b.cell_start, b.cell_fill, b.perm, g);
-  if (b.cell_rows)
-    hipLaunchKernelGGL(k_cell_sort, dim3(div_up(b.n_cells, kBlock / 64)), dim3(kBlock), 0, s, b.cell_start,
-                       b.cell_count, b.cell_fill, b.n_cells, b.ext_src, b.perm, g);
-  hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
 }
 
 void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, const int32_t* types2,
@@ -1467,17 +1458,202 @@ void launch_copy_gated_i32(int32_t* dst, const int32_t* src, int64_t n, const in
 
 int64_t type_row_blocks(int64_t N) { return div_up(N, kBlock); }
 
-void launch_type_rows(const int32_t* types, int64_t N, int32_t T, int32_t per_type,
-                      int32_t* tblk, int32_t* tex, int32_t* toff, int32_t* rows,
-                      int64_t rows_len, const int32_t* gate, hipStream_t s) {
-  const int32_t Tn = per_type ? T : 1;
-  const int32_t nb = (int32_t)type_row_blocks(N);
-  hipLaunchKernelGGL(k_type_block_count, dim3(nb), dim3(kBlock), 0, s, types, N, Tn, per_type, nb,
-                     tblk, rows, rows_len, gate);
-  hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, tblk, tex, Tn * nb, gate);
-  hipLaunchKernelGGL(k_type_shift, dim3(1), dim3(64), 0, s, tex, N, Tn, nb, toff, gate);
-  hipLaunchKernelGGL(k_type_block_scatter, dim3(nb), dim3(kBlock), 0, s, types, N, Tn, per_type,
-                     nb, tex, toff, rows, gate);
+// A thread block of 1024 orders the atoms of a call this small by itself.
+// Bound by the latency of its few dependent passes: LDS holds the cell
+// counts and the caller indices in cell order; each atom's place in its cell
+// is the number of smaller caller indices there, so the order is that of the
+// other kernels.  Two launches (k_gather_atoms moves the atoms: with their
+// scattered stores in the block they were no faster) for the others' nine, each
+// of which is mostly its own launch at these sizes.
+constexpr int kOneThreads = 1024, kOnePerThread = 6;
+constexpr int kOneAtoms = kOneThreads * kOnePerThread;  // atoms, and cells
+
+__global__ void __launch_bounds__(kOneThreads) k_order_one_block(BuildArgs b) {
+  constexpr int kWaves = kOneThreads / 64, P = kOnePerThread;
+  __shared__ int32_t cell[kOneAtoms], ext[kOneAtoms];
+  __shared__ int32_t wsum[kWaves], wtypes[kWaves][kMaxTypes], base[kMaxTypes];
+  if (gated_off(b.gate)) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int N = (int)b.N;
+  const int turns = (N + kOneThreads - 1) / kOneThreads;  // atoms of a thread: t, t + 1024, ...
+  // every pass below loads for all of a thread's atoms before it uses any of them
+  double x[P], y[P], z[P];
+  int32_t type[P], sid[P], mine[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    const int e = min(t + q * kOneThreads, N - 1);
+    x[q] = b.pos_ext[e];
+    y[q] = b.pos_ext[N + e];
+    z[q] = b.pos_ext[2 * N + e];
+    type[q] = b.types_ext[e];
+    sid[q] = struct_of(b, e);
+    mine[q] = b.ext_src ? b.ext_src[e] : e;  // its caller index
+  }
+  for (int c = t; c < b.n_cells; c += kOneThreads) cell[c] = 0;
+  if (b.check && t < 8) {
+    b.check[t] = 0;
+    __threadfence();  // before other threads' atomics on them
+  }
+  __syncthreads();
+  int key[P];   // cell of the thread's atoms; ~cell in a structure without cells, whose atoms keep
+  int from[P];  // their order from its first
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    const int e = t + q * kOneThreads;
+    const StructInfo& st = b.structs[sid[q]];
+    from[q] = (int)st.start;
+    key[q] = ~st.cell_off;
+    if (st.mode == kModeCells) key[q] = cell_of(st, x[q], y[q], z[q]);
+    if (e >= N) continue;
+    if (key[q] >= 0) atomicAdd(&cell[key[q]], 1);
+    else if (e == st.start) cell[st.cell_off] = (int32_t)st.count;
+  }
+  __syncthreads();
+  // exclusive scan of the counts, a run of cells to a thread
+  {
+    const int per = (b.n_cells + kOneThreads - 1) / kOneThreads, lo = min(t * per, b.n_cells),
+              hi = min(lo + per, b.n_cells);
+    int32_t sum = 0;
+    for (int c = lo; c < hi; ++c) sum += cell[c];
+    int32_t run = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t v = __shfl_up(run, off);
+      if (lane >= off) run += v;
+    }
+    if (lane == 63) wsum[w] = run;
+    __syncthreads();
+    run -= sum;
+    for (int v = 0; v < w; ++v) run += wsum[v];
+    for (int c = lo; c < hi; ++c) {
+      const int32_t n = cell[c];
+      b.cell_start[c] = run;
+      b.cell_count[c] = n;
+      cell[c] = run;
+      run += n;
+    }
+  }
+  __syncthreads();
+  int begin[P];  // first place of the atom's cell
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    begin[q] = b.cell_start[key[q] < 0 ? ~key[q] : key[q]];
+  }
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    if (t + q * kOneThreads < N && key[q] >= 0) ext[atomicAdd(&cell[key[q]], 1)] = mine[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    const int e = t + q * kOneThreads;
+    if (e >= N) continue;
+    int k = begin[q];
+    if (key[q] < 0) {
+      k += e - from[q];
+    } else {
+      const int end = cell[key[q]];  // where its last atom went
+      for (int p = begin[q]; p < end; p += 4) {
+        int32_t other[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) other[u] = ext[min(p + u, end - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) k += p + u < end && other[u] < mine[q] ? 1 : 0;
+      }
+    }
+    begin[q] = k;  // from here on: its place
+  }
+  __syncthreads();
+  const int Tn = b.per_type ? b.n_types : 1;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q >= turns) break;
+    const int e = t + q * kOneThreads;
+    if (e < N) cell[begin[q]] = e | (b.per_type ? min(max(type[q], 0), Tn - 1) : 0) << 16;
+  }
+  __syncthreads();
+  int sp[P];  // species of the internal atoms t, t + 1024, ...
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int k = t + q * kOneThreads;
+    sp[q] = -1;
+    if (k >= N) continue;
+    b.perm[k] = cell[k] & 0xffff;
+    sp[q] = cell[k] >> 16;
+  }
+  if (!b.rows) return;
+  // the species-grouped rows: species counts, their starts, then ranks in internal order
+  for (int64_t r = t; r < b.rows_len; r += kOneThreads) b.rows[r] = -1;
+  if (t < kMaxTypes) base[t] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < P; ++q)
+    for (int s = 0; s < Tn; ++s) {
+      const uint64_t m = __ballot(sp[q] == s);
+      if (lane == 0 && m) atomicAdd(&base[s], (int32_t)__popcll(m));
+    }
+  __syncthreads();
+  if (t == 0) {
+    int32_t o = 0;
+    for (int s = 0; s < Tn; ++s) {
+      const int32_t n = base[s];
+      base[s] = o;
+      o += (n + kRowGroup - 1) / kRowGroup * kRowGroup;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (q * kOneThreads >= N) break;
+    int rank = 0;
+    for (int s = 0; s < Tn; ++s) {
+      const uint64_t m = __ballot(sp[q] == s);
+      if (sp[q] == s) rank = lanes_below(m);
+      if (lane == 0) wtypes[w][s] = __popcll(m);
+    }
+    __syncthreads();
+    if (sp[q] >= 0) {
+      for (int v = 0; v < w; ++v) rank += wtypes[v][sp[q]];
+      b.rows[base[sp[q]] + rank] = t + q * kOneThreads;
+    }
+    __syncthreads();
+    if (t < Tn)
+      for (int v = 0; v < kWaves; ++v) base[t] += wtypes[v][t];
+    __syncthreads();
+  }
+}
+
+void launch_order_atoms(const BuildArgs& b, hipStream_t s) {
+  const int32_t* g = b.gate;
+  // one block up to the size where the chip's share of the work makes up for the launches:
+  // 12 us against 28 for 256 atoms, 20 : 41 for 2,048, 28 : 42 for 4,000, 35 : 41 for 5,324,
+  // 42 : 40 for 6,912 (and its LDS holds a word per cell and per atom)
+  if (b.N <= kOneAtoms && b.n_cells <= kOneAtoms) {
+    hipLaunchKernelGGL(k_order_one_block, dim3(1), dim3(kOneThreads), 0, s, b);
+    hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
+    return;
+  }
+  hipLaunchKernelGGL(k_fill_cells, grid_for(std::max<int64_t>(b.n_cells, 8)), dim3(kBlock), 0, s, b);
+  hipLaunchKernelGGL(k_cell_key, grid_for(b.N), dim3(kBlock), 0, s, b);
+  hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, b.cell_count, b.cell_start, b.n_cells, g);
+  hipLaunchKernelGGL(k_cell_scatter, grid_for(b.N), dim3(kBlock), 0, s, b);
+  if (b.cell_rows)
+    hipLaunchKernelGGL(k_cell_sort, dim3(div_up(b.n_cells, kBlock / 64)), dim3(kBlock), 0, s, b.cell_start,
+                       b.cell_count, b.cell_fill, b.n_cells, b.ext_src, b.perm, g);
+  hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
+  if (!b.rows) return;
+  const int32_t Tn = b.per_type ? b.n_types : 1;
+  const int32_t nb = (int32_t)type_row_blocks(b.N);
+  hipLaunchKernelGGL(k_type_block_count, dim3(nb), dim3(kBlock), 0, s, b.types, b.N, Tn, b.per_type, nb, b.tblk,
+                     b.rows, b.rows_len, g);
+  hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, b.tblk, b.tex, Tn * nb, g);
+  hipLaunchKernelGGL(k_type_block_scatter, dim3(nb), dim3(kBlock), 0, s, b.types, b.N, Tn, b.per_type, nb, b.tex,
+                     b.rows, g);
 }
 
 }  // namespace nep

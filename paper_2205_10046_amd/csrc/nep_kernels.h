@@ -9,7 +9,7 @@ struct BuildArgs {
   int32_t n_cells;
   const double* pos_ext;      // caller order [3][N]
   const int32_t* types_ext;
-  const int32_t* sid_ext;
+  const int32_t* sid_ext;     // structure of each source atom (not read when n_struct is 1)
   const int32_t* ext_src;     // caller index of each source atom (NULL: the source index)
   const StructInfo* structs;
   int32_t* key;               // [N]
@@ -33,6 +33,15 @@ struct BuildArgs {
   double* vel_dst = nullptr;
   const int32_t* ext_in = nullptr;
   int32_t* ext_out = nullptr;
+  // optional: clear check[0..7], then set check[3] for a species outside [0, n_types)
+  // and check[4] for a position that is not finite
+  int32_t* check = nullptr;
+  int32_t n_types = 0;
+  // the network's species-grouped row order of the ordered atoms (rows NULL: not made);
+  // tblk and tex hold kMaxTypes * type_row_blocks(N) ints each
+  int32_t per_type = 0;
+  int32_t *tblk = nullptr, *tex = nullptr, *rows = nullptr;
+  int64_t rows_len = 0;
 };
 
 struct EvalArgs {
@@ -69,6 +78,7 @@ struct EvalArgs {
 void launch_fill_i32(int32_t* a, int64_t n, int32_t v, hipStream_t s);
 void launch_assign_struct(const int64_t* offs, int32_t n_struct, int64_t N, int32_t* sid,
                           hipStream_t s);
+// Internal order of the atoms and everything that follows from it.
 void launch_order_atoms(const BuildArgs& b, hipStream_t s);
 // Exact rows L at the cutoffs of b with their reverse index, every row
 // invariant checked (flags [2] and [6]); V's rows serve as scratch.
@@ -98,12 +108,7 @@ void launch_copy_gated_f64(double* dst, const double* src, int64_t n, const int3
                            hipStream_t s);
 void launch_copy_gated_i32(int32_t* dst, const int32_t* src, int64_t n, const int32_t* gate,
                            hipStream_t s);
-// Species-grouped row order of the network pass; tblk and tex hold
-// kMaxTypes * type_row_blocks(N) ints each.
 int64_t type_row_blocks(int64_t N);
-void launch_type_rows(const int32_t* types, int64_t N, int32_t T, int32_t per_type,
-                      int32_t* tblk, int32_t* tex, int32_t* toff, int32_t* rows,
-                      int64_t rows_len, const int32_t* gate, hipStream_t s);
 
 // descriptor.hip / force.hip: return false if no kernel exists for the model
 bool launch_descriptor(const EvalArgs& a, hipStream_t s);
@@ -188,7 +193,6 @@ void launch_unpermute_md(const int32_t* perm, int64_t N, const double* pos_int,
                          const double* vel_int, double* pos_ext, double* vel_ext,
                          hipStream_t s);
 void launch_check_finite(const double* a, int64_t n, int32_t* flag, hipStream_t s);
-void launch_check_types(const int32_t* types, int64_t n, int32_t T, int32_t* flag, hipStream_t s);
 void launch_srv_kick_drift(int64_t N, double* pos, double* vel, const double* F, const double* hdm,
                            const double* dta, const uint8_t* move, hipStream_t s);
 void launch_srv_kick(int64_t N, double* vel, const double* F, const double* hdm, const uint8_t* move,
