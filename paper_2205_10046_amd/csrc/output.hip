@@ -173,15 +173,18 @@ void launch_struct_totals_chunked(const float* U, const float* W, int64_t N, con
 
 __global__ void k_descriptors_out(const float* __restrict__ q, int64_t N, int NDp, int ND,
                                   const int32_t* __restrict__ perm, double* __restrict__ out) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  // a thread to a value: both sides in runs of ND (a thread to an atom: 16.7 us for the 6,912
+  // atoms of the 4-species alloy, this 3.9)
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = x / ND;
   if (k >= N) return;
-  const int64_t e = perm[k];
-  for (int d = 0; d < ND; ++d) out[e * ND + d] = (double)q[k * NDp + d];
+  const int d = (int)(x - k * ND);
+  out[perm[k] * (int64_t)ND + d] = (double)q[k * NDp + d];
 }
 
 void launch_descriptors_out(const float* q, int64_t N, int NDp, int ND, const int32_t* perm,
                             double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_descriptors_out, dim3(div_up(N, kBlock)), dim3(kBlock), 0, s, q, N, NDp,
+  hipLaunchKernelGGL(k_descriptors_out, dim3(div_up(N * ND, kBlock)), dim3(kBlock), 0, s, q, N, NDp,
                      ND, perm, out);
 }
 

@@ -284,7 +284,7 @@ class Handle:
         pos, types, box = _f64(pos), _i32(types), _f64(box)
         pbc = _i32(np.ones(3) if pbc is None else pbc)
         n = pos.shape[1]
-        U, F, W, T = np.zeros(n), np.zeros((3, n)), np.zeros((9, n)), np.zeros(10)
+        U, F, W, T = np.empty(n), np.empty((3, n)), np.empty((9, n)), np.empty(10)
         self._check(load().nep_compute(
             self._h, n, _ptr(pos, C.c_double), _ptr(types, C.c_int32), _ptr(box, C.c_double),
             _ptr(pbc, C.c_int32), _ptr(U, C.c_double), _ptr(F, C.c_double),
@@ -346,7 +346,7 @@ class Handle:
         pos, types, box = _f64(pos), _i32(types), _f64(box)
         pbc = _i32(np.ones(3) if pbc is None else pbc)
         n = pos.shape[1]
-        q = np.zeros((n, self.n_des))
+        q = np.empty((n, self.n_des))
         self._check(load().nep_descriptors(
             self._h, n, _ptr(pos, C.c_double), _ptr(types, C.c_int32), _ptr(box, C.c_double),
             _ptr(pbc, C.c_int32), _ptr(q, C.c_double)))
