@@ -20,13 +20,35 @@
 // gradients would not fit one lane: D alone is 168 registers.
 // Gather: F_i = sum_j dU_i/dr_ij - dU_j/dr_ji and W_i = sum_j r_ij (x)
 //   dU_j/dr_ji over the radial row, reading dU_j/dr_ji through the reverse
-//   index: no atomics, so results are bitwise reproducible.
+//   index: no atomics, so results are bitwise reproducible.  The first sum
+//   comes from the force pass.  Bound by the cache lines its reads touch: the
+//   partial forces lie in rows of an atom, where the entries next to the one
+//   an atom reads belong to the atoms next to it (131,072 atoms: 73 us with
+//   the entries of neighbouring atoms side by side and both sums read, 68 with
+//   one sum, 58 in rows; 2,000,000 atoms: 1295, 1208, 1064).
 #include "pair.h"
 
 namespace nep {
 
+// Sum of v over the G adjacent lanes of one atom (4 or 16); every lane of the
+// group gets the same bits (the pairwise adds commute).
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
+  if constexpr (G == 16) {  // the mirrored half row, then the mirrored row
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
+  }
+  return v;
+}
+
+// Three waves per SIMD where D leaves the registers for them: 72 words of it do
+// with two or three spilled (132,000 atoms of the 3-species training model: 171 us
+// against 193 with two waves), the 96 of n_A = 8, l_max = 6 would spill 18 (2.94 ms
+// against 2.66 for 2,000,000 atoms).
 template <int NT, int L, bool BATCH, int Q, int SH>
-__global__ void __launch_bounds__(kBlock, 2) k_partial_forces(EvalArgs a, StructInfo st0) {
+__global__ void __launch_bounds__(kBlock, NT * num_poly(L) <= 72 ? 3 : 2) k_partial_forces(EvalArgs a, StructInfo st0) {
   constexpr int NB = num_poly(L), NBT = (NB + 3) / 4;
   constexpr int kAtoms = 64 / (4 * Q);  // atoms of a wave
   using Sh = BasisShape<SH>;
@@ -258,20 +280,34 @@ __global__ void __launch_bounds__(kBlock, 2) k_partial_forces(EvalArgs a, Struct
     return (v - (x * Vx + y * Vy + z * Vz) * rinv) * rinv;  // v u + (V - (u V) u) / r
   };
   // ---- the row: the radial part of every entry, the angular part of the prefix.  A result is
-  // stored while the next entry is computed, so no step waits for its own store ----
+  // stored while the next entry is computed, so no step waits for its own store; their sum is
+  // the atom's own part of its force, which the gather then need not read again ----
   float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
   int64_t out_e = -1;
+  float own[3] = {0.f, 0.f, 0.f};
+  auto put = [&]() __attribute__((always_inline)) {
+    if (out_e < 0) return;
+    a.P[out_e] = out;
+    own[0] += out.x;
+    own[1] += out.y;
+    own[2] += out.z;
+  };
   walk_row<BATCH>(a, fr, i, sub, nnR, 4 * Q, steps,
                   [&](int k, int m, int64_t e, int32_t tj, float fx, float fy, float fz) __attribute__((always_inline)) {
-    if (out_e >= 0) a.P[out_e] = out;
+    put();
     float r, rinv;
     length_of(fx * fx + fy * fy + fz * fz, r, rinv);
     float along = radial_scalar(tj, r, rinv), Vx = 0.f, Vy = 0.f, Vz = 0.f;
     if (k < stepsA) along += angular(tj, r, rinv, fx * rinv, fy * rinv, fz * rinv, m < nnA ? 1.f : 0.f, Vx, Vy, Vz);
     out = make_float4(along * fx + Vx * rinv, along * fy + Vy * rinv, along * fz + Vz * rinv, 0.f);
-    out_e = m < nnR ? e : -1;
+    out_e = m < nnR ? i * a.L.MR + m : -1;
   });
-  if (out_e >= 0) a.P[out_e] = out;
+  put();
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const float v = group_sum<4 * Q>(own[c]);
+    if (c == sub && live) a.F[(int64_t)c * N + i] = v;
+  }
 }
 
 bool launch_partial_forces(const EvalArgs& a, hipStream_t s) {
@@ -291,22 +327,9 @@ bool launch_partial_forces(const EvalArgs& a, hipStream_t s) {
 // force and virial gather (eqs. F_ij, F_i, virial)
 // ---------------------------------------------------------------------------
 
-// Sum of v over the G adjacent lanes of one atom (4 or 16); every lane of the
-// group gets the same bits (the pairwise adds commute).
-template <int G>
-__device__ __forceinline__ float group_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
-  if constexpr (G == 16) {  // the mirrored half row, then the mirrored row
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
-  }
-  return v;
-}
-
 // G lanes per atom (4 or 16) walk its radial row (lane s takes entries
-// s, s + G, ...); dU_j/dr_ji sits at position rev[m][i] of row j.  The index
-// words of a lane's entry after next and the partial forces (and neighbour
+// s, s + G, ...); dU_j/dr_ji sits at position rev[m][i] of row j, and F holds
+// sum_j dU_i/dr_ij.  The index words of a lane's entry after next and the partial forces (and neighbour
 // position, for the virial) of its next entry are loaded while the current
 // one is accumulated; the lane sums are combined with DPP sums.  Four lanes
 // read whole 64-byte runs of a row; sixteen, where a quad per atom leaves
@@ -344,8 +367,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
     return w;
   };
   Words w0 = words(sub), w1 = words(sub + G);
-  float4 pij = a.P[(int64_t)min(sub, max(nn - 1, 0)) * N + i];
-  float4 pji = a.P[(int64_t)w0.r * N + w0.j];
+  float4 pji = a.P[(int64_t)w0.j * a.L.MR + w0.r];
   double px = 0.0, py = 0.0, pz = 0.0;
   float4 dq = make_float4(0.f, 0.f, 0.f, 0.f);
   if (VIRIAL && BATCH) dq = a.disp[(int64_t)min(sub, max(nn - 1, 0)) * N + i];
@@ -357,22 +379,21 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
   float F[3] = {0.f, 0.f, 0.f}, W[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int m = sub; m < nn; m += G) {
     const Words c = w0;
-    const float4 cij = pij, cji = pji;
+    const float4 cji = pji;
     const double cx = px, cy = py, cz = pz;
     const float4 cd = dq;
     w0 = w1;
     w1 = words(m + 2 * G);
-    pij = a.P[(int64_t)min(m + G, nn - 1) * N + i];
-    pji = a.P[(int64_t)w0.r * N + w0.j];
+    pji = a.P[(int64_t)w0.j * a.L.MR + w0.r];
     if (VIRIAL && BATCH) dq = a.disp[(int64_t)min(m + G, nn - 1) * N + i];
     if (VIRIAL && !BATCH) {
       px = pos[w0.j];
       py = pos[N + w0.j];
       pz = pos[2 * N + w0.j];
     }
-    F[0] += cij.x - cji.x;
-    F[1] += cij.y - cji.y;
-    F[2] += cij.z - cji.z;
+    F[0] += cji.x;
+    F[1] += cji.y;
+    F[2] += cji.z;
     if constexpr (VIRIAL) {
       float d[3] = {cd.x, cd.y, cd.z};
       if constexpr (!BATCH) {
@@ -407,8 +428,9 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const float v = group_sum<G>(F[c]);
-    if (c % G == sub) {
+    const float other = group_sum<G>(F[c]);
+    if (c == sub) {
+      const float v = a.F[(int64_t)c * N + i] - other;  // the atom's own part is there
       a.F[(int64_t)c * N + i] = v;
       if (a.kick_vel) a.kick_vel[(int64_t)c * N + i] += 0.5 * a.kick_dt * a.kick_inv_mass[a.types[i]] * (double)v;
     }

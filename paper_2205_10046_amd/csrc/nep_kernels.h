@@ -56,7 +56,7 @@ struct EvalArgs {
   float* fp;                  // [N][NDp]
   float* U;                   // [N]
   float* sums;                // [tiles][N][4][4], see pair.h
-  float4* P;                  // [MR][N] dU_i/dr_ij per radial entry
+  float4* P;                  // [N][MR] dU_i/dr_ij per radial entry
   const float4* disp;         // [MR][N] displacement and species (as bits) per entry (batches)
   float* F;                   // [3][N] internal
   float* W;                   // [9][N] internal
