@@ -1000,11 +1000,16 @@ const Tuning& pick_shape(nep_handle* h, const Prepared& pp) {
 
 // Descriptors, network, partial forces and the force gather; the per-atom
 // virial only when `virial` (MD steps without a thermo row skip it).
+// `filtered`: the rows come from skin_filter.
 void forces(nep_handle* h, const Prepared& pp, hipStream_t s, const DevModel* model = nullptr,
-            bool virial = true, const MDArgs* kick = nullptr) {
+            bool virial = true, const MDArgs* kick = nullptr, bool filtered = false) {
   const Tuning& t = pick_shape(h, pp);
   EvalArgs a = eval_args(h, pp, model ? *model : h->M);
   a.quads = t.quads;
+  if (filtered && rev_in_candidates(pp.N, pp.batch)) {
+    a.fmap = h->V.fmap;
+    a.rev_err = h->flags + 2;
+  }
   {
     Stage st(h, "descriptor", s);
     if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
@@ -2309,7 +2314,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
     skin_rebuild(h, pp, rl, nullptr, s, mu_cum);
     skin_filter(h, pp, s);
     launch_fill_i32(h->flags + 6, 1, 0, s);
-    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, h->flags + 6, s);
+    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, rev_in_candidates(N, pp.batch) ? &h->V : nullptr, h->flags + 6, s);
     const int32_t* fl = read_flags(h, s);
     if (fl[3]) throw Failure{NEP_E_INVALID_ARG, "an atom type is out of range"};
     if (fl[4]) throw Failure{NEP_E_NONFINITE, "positions contain NaN or Inf"};
@@ -2320,7 +2325,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
     }
     if (attempt == 3) throw Failure{NEP_E_NEIGHBOR_OVERFLOW, "neighbour rows kept overflowing"};
   }
-  if (!cont) forces(h, pp, s);
+  if (!cont) forces(h, pp, s, nullptr, true, nullptr, true);
   MDArgs md{};
   md.N = N;
   md.F = h->F;
@@ -2372,7 +2377,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
       Stage st(h, "neighbor_rows", cs);
       skin_filter(h, pp, cs);
     }
-    forces(h, pp, cs, nullptr, virial || npt, &md);  // the gather applies the second half kick
+    forces(h, pp, cs, nullptr, virial || npt, &md, true);  // the gather applies the second half kick
     if (ens) {
       Stage st(h, "ensemble", cs);
       launch_ens_kinetic(h->vel, h->types, h->mass, N, kAmuA2fs2, h->ens_partial, est, cs);
@@ -2485,7 +2490,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
       // half kick uses are evaluated again in the new order
       skin_rebuild(h, pp, rl, nullptr, s, mu_cum);
       skin_filter(h, pp, s);
-      forces(h, pp, s);
+      forces(h, pp, s, nullptr, true, nullptr, true);
       redo = false;
     }
     if (use_graph || ens) {
@@ -2514,7 +2519,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
       }
     }
     launch_check_finite(h->pos, 3 * N, h->flags + 4, s);
-    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, h->flags + 6, s);
+    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, rev_in_candidates(N, pp.batch) ? &h->V : nullptr, h->flags + 6, s);
     if (npt)  // the current cell, read with the flags
       HIPCHK(hipMemcpyAsync(h->pinned + 1536, h->structs, sizeof(StructInfo), hipMemcpyDeviceToHost, s));
     const int32_t* fl = read_flags(h, s);
@@ -2723,7 +2728,7 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       }
     }
     launch_check_finite(h->pos, 3 * N, h->flags + 4, s);
-    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, h->flags + 6, s);
+    launch_check_rows(N, h->sid, h->structs, pp.geo.st, pp.batch, h->L, nullptr, h->flags + 6, s);
     int32_t* fl = (int32_t*)(h->pinned + kPinFlags);
     HIPCHK(hipMemcpyAsync(fl, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));

@@ -337,7 +337,7 @@ bool launch_partial_forces(const EvalArgs& a, hipStream_t s) {
 // virial, 12.1 : 7.6 at 4,000 atoms, 12.5 : 12.5 at 10,976, 19.5 : 17.3 at
 // 19,652, 20.8 : 25.8 at 32,000; without it 9.3 : 4.6 at 2,048.
 // VIRIAL = false leaves W untouched (MD steps without a thermo row).
-template <bool BATCH, bool VIRIAL, int G>
+template <bool BATCH, bool VIRIAL, bool CAND, int G>
 __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
   const int64_t N = a.N;
   const int sub = threadIdx.x & (G - 1);
@@ -366,8 +366,27 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
     }
     return w;
   };
-  Words w0 = words(sub), w1 = words(sub + G);
-  float4 pji = a.P[(int64_t)w0.j * a.L.MR + w0.r];
+  // position of the entry in its partner's row: with CAND through the filter's map of the
+  // partner's candidates (its -1 is an entry without a partner: an error, kept in bounds)
+  bool broken = false;
+  auto position = [&](const Words& w) -> int32_t {
+    if constexpr (CAND) return a.fmap[(int64_t)w.r * N + w.j];
+    else return w.r;
+  };
+  auto partial = [&](const Words& w, int32_t p, bool in) -> float4 {
+    if constexpr (CAND) {
+      broken = broken || (in && p < 0);
+      p = min(max(p, 0), a.L.MR - 1);
+    }
+    return a.P[(int64_t)w.j * a.L.MR + p];
+  };
+  Words w0 = words(sub), w1 = words(sub + G), w2;
+  int32_t p1 = position(w0);
+  float4 pji = partial(w0, p1, sub < nn);
+  if constexpr (CAND) {
+    w2 = words(sub + 2 * G);
+    p1 = position(w1);
+  }
   double px = 0.0, py = 0.0, pz = 0.0;
   float4 dq = make_float4(0.f, 0.f, 0.f, 0.f);
   if (VIRIAL && BATCH) dq = a.disp[(int64_t)min(sub, max(nn - 1, 0)) * N + i];
@@ -383,8 +402,15 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
     const double cx = px, cy = py, cz = pz;
     const float4 cd = dq;
     w0 = w1;
-    w1 = words(m + 2 * G);
-    pji = a.P[(int64_t)w0.j * a.L.MR + w0.r];
+    if constexpr (CAND) {
+      w1 = w2;
+      w2 = words(m + 3 * G);
+      pji = partial(w0, p1, m + G < nn);
+      p1 = position(w1);
+    } else {
+      w1 = words(m + 2 * G);
+      pji = partial(w0, w0.r, true);
+    }
     if (VIRIAL && BATCH) dq = a.disp[(int64_t)min(m + G, nn - 1) * N + i];
     if (VIRIAL && !BATCH) {
       px = pos[w0.j];
@@ -442,17 +468,21 @@ __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
       if (v % G == sub) a.W[(int64_t)v * N + i] = x;
     }
   }
+  if (CAND && broken) atomicExch(a.rev_err, 1);
 }
 
 template <int G>
 static void launch_gather_g(const EvalArgs& a, bool virial, hipStream_t s) {
   dim3 grid((unsigned)div_up(a.N * G, kBlock));
   if (a.batch) {
-    if (virial) hipLaunchKernelGGL((k_gather<true, true, G>), grid, dim3(kBlock), 0, s, a, a.st0);
-    else hipLaunchKernelGGL((k_gather<true, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+    if (virial) hipLaunchKernelGGL((k_gather<true, true, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+    else hipLaunchKernelGGL((k_gather<true, false, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+  } else if (a.fmap) {
+    if (virial) hipLaunchKernelGGL((k_gather<false, true, true, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+    else hipLaunchKernelGGL((k_gather<false, false, true, G>), grid, dim3(kBlock), 0, s, a, a.st0);
   } else {
-    if (virial) hipLaunchKernelGGL((k_gather<false, true, G>), grid, dim3(kBlock), 0, s, a, a.st0);
-    else hipLaunchKernelGGL((k_gather<false, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+    if (virial) hipLaunchKernelGGL((k_gather<false, true, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
+    else hipLaunchKernelGGL((k_gather<false, false, false, G>), grid, dim3(kBlock), 0, s, a, a.st0);
   }
 }
 

@@ -1180,7 +1180,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
         fmap[e] = p;
         if (p < L.MR) {
           lnl[(int64_t)p * N + i] = jn[u];
-          lrev[(int64_t)p * N + i] = rn[u];  // candidate position, resolved by the next kernel
+          lrev[(int64_t)p * N + i] = rn[u];  // candidate position, resolved by its reader
           if (images) lcd[(int64_t)p * N + i] = cn[u];
         }
       }
@@ -1200,8 +1200,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
 // rev of the exact rows: the filter left in L.revR[p][i] the candidate
 // position of i in the row of j = L.nlR[p][i]; the exact position there is
 // V.fmap of that candidate entry, written in place.  G lanes per atom
-// take exact entries p = s, s + G, ..., four or sixteen as in the filter (2,048
-// atoms: 6.6 us with four lanes, 4.1 with sixteen); a lane loads the words of kFilterChunk entries, then their map
+// take exact entries p = s, s + G, ..., four or sixteen as in the filter; a lane loads the words of kFilterChunk entries, then their map
 // entries, then writes them.  For a batch (DISP) it also writes every
 // entry's float32 displacement and species (as bits), read by each parameter
 // set's passes.
@@ -1312,6 +1311,7 @@ constexpr int kCheckChunk = 4;  // entries a lane checks together
 __global__ void __launch_bounds__(kBlock) k_check_rows(int64_t N, const int32_t* __restrict__ sid,
                                                        const StructInfo* __restrict__ structs,
                                                        StructInfo st0, int32_t batch, Lists L,
+                                                       const int32_t* __restrict__ fmap, int32_t MV,
                                                        int32_t* __restrict__ bad) {
   constexpr int G = kCheckLanes, U = kCheckChunk;
   const int sub = threadIdx.x & (G - 1);
@@ -1343,6 +1343,7 @@ __global__ void __launch_bounds__(kBlock) k_check_rows(int64_t N, const int32_t*
     for (int u = 0; u < U; ++u) {
       jok[u] = m0 + u * G < nn && j[u] >= lo && j[u] < hi;
       if (m0 + u * G < nn && !jok[u]) b |= 2;
+      if (fmap && jok[u]) r[u] = r[u] >= 0 && r[u] < MV ? fmap[(int64_t)r[u] * N + j[u]] : -1;
     }
     int nj[U];
 #pragma unroll
@@ -1373,10 +1374,15 @@ __global__ void __launch_bounds__(kBlock) k_check_rows(int64_t N, const int32_t*
 }
 
 void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs, const StructInfo& st0,
-                       bool batch, const Lists& L, int32_t* bad, hipStream_t s) {
+                       bool batch, const Lists& L, const Lists* V, int32_t* bad, hipStream_t s) {
   hipLaunchKernelGGL(k_check_rows, grid_for(N * kCheckLanes), dim3(kBlock), 0, s, N, sid, structs, st0,
-                     (int32_t)(batch ? 1 : 0), L, bad);
+                     (int32_t)(batch ? 1 : 0), L, V ? V->fmap : nullptr, V ? V->MR : 0, bad);
 }
+
+// Few atoms: the gather looks the positions up itself, a launch less (a step of
+// 5,323 atoms 89 -> 86 us).  Many: its random reads of the map would fill the caches
+// that it reads the partial forces through (131,072 atoms: 124 us against 43 + 58).
+bool rev_in_candidates(int64_t N, bool batch) { return !batch && N < kFewAtoms; }
 
 template <int G>
 static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V, const Lists& L,
@@ -1388,10 +1394,10 @@ static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batc
   else
     hipLaunchKernelGGL((k_filter_rows<false, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
                        st0, V, b.rcR2, b.rcA2, L, b.overflow);
-  if (b.disp)
+  if (batch)
     hipLaunchKernelGGL((k_reverse_from_candidates<true, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        b.pos, b.types, b.sid, b.structs, b.disp, b.overflow + 2);
-  else
+  else if (!rev_in_candidates(b.N, batch))
     hipLaunchKernelGGL((k_reverse_from_candidates<false, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        (const double*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr,
                        (const StructInfo*)nullptr, (float4*)nullptr, b.overflow + 2);

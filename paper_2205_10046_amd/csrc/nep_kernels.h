@@ -51,6 +51,10 @@ struct EvalArgs {
   const int32_t* sid;
   const StructInfo* structs;
   Lists L;                    // exact rows
+  // rows filtered from candidates: L.revR holds the candidate position of the reverse
+  // entry and fmap [MV][N] the exact position of every candidate (NULL: L.revR is that)
+  const int32_t* fmap;
+  int32_t* rev_err;           // set when a candidate has none
   DevModel M;
   float* q;                   // [N][NDp]
   float* fp;                  // [N][NDp]
@@ -85,9 +89,10 @@ void launch_order_atoms(const BuildArgs& b, hipStream_t s);
 void launch_build_rows(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s);
 void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate, hipStream_t s);
 // Sets bits of *bad when the exact rows break an invariant the evaluation
-// kernels rely on for in-bounds access (see neighbor.hip).
+// kernels rely on for in-bounds access (see neighbor.hip).  V: the candidates
+// of rows whose reverse positions are theirs (NULL: positions in L).
 void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs, const StructInfo& st0,
-                       bool batch, const Lists& L, int32_t* bad, hipStream_t s);
+                       bool batch, const Lists& L, const Lists* V, int32_t* bad, hipStream_t s);
 void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s);
 // After a gated re-sort: pos/vel/types/ext <- their permuted copies, pos_ref <- pos
 // (and *count += 1 when count is given).
@@ -95,6 +100,8 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
                            const int32_t* ext2, double* pos, double* vel, int32_t* types, int32_t* ext,
                            double* pos_ref, const int32_t* gate, hipStream_t s,
                            double* mu_cum = nullptr, int32_t* count = nullptr);
+// Whether launch_filter_rows leaves the candidates' reverse positions in L.revR.
+bool rev_in_candidates(int64_t N, bool batch);
 void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
                         const Lists& L, hipStream_t s);
 // flag = 1 if an atom moved more than allowed since the last build, or will
