@@ -396,6 +396,7 @@ struct nep_handle {
   // upload, rewritten only after the previous upload (tab_event) has read it
   unsigned char* pinned_tab = nullptr;
   size_t pinned_tab_cap = 0;
+  hipEvent_t flags_event = nullptr;  // the flags of a call's rows are in `pinned`
   hipEvent_t tab_event = nullptr;
   // timing
   bool timing = false;
@@ -450,6 +451,8 @@ struct nep_handle {
     io_cap = 0;
     if (tab_event) (void)hipEventDestroy(tab_event);
     tab_event = nullptr;
+    if (flags_event) (void)hipEventDestroy(flags_event);
+    flags_event = nullptr;
     dev_free(loss_part); dev_free(loss_offs); dev_free(snes_util); dev_free(heat_part);
     dev_free(ens_state); dev_free(ens_partial);
     ens_partial_cap = 0;
@@ -932,23 +935,46 @@ void with_type_rows(nep_handle* h, BuildArgs& b) {
 
 // Rows for the current internal positions, after launch_order_atoms cleared and
 // set the flags; grows the capacities (auto mode) or fails (fixed
-// capacities) when a row overflows.  Synchronises once.
-void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, hipStream_t s) {
+// capacities) when a row overflows.  eval() launches what follows from the
+// rows and writes the handle's own buffers only: it is on its way before the
+// host has read the flags, so the device does not wait for that, and its
+// kernels do nothing when a flag is set.  Synchronises with the flags.
+template <class Eval>
+void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, hipStream_t s, Eval&& eval) {
+  if (!h->flags_event) HIPCHK(hipEventCreateWithFlags(&h->flags_event, hipEventDisableTiming));
+  struct Drain {  // a failing call leaves nothing behind it in flight
+    hipStream_t s;
+    bool armed = true;
+    ~Drain() {
+      if (armed) (void)hipStreamSynchronize(s);
+    }
+  } drain{s};
   for (int attempt = 0; attempt < 3; ++attempt) {
-    if (attempt) launch_fill_i32(h->flags, 8, 0, s);
+    if (attempt) {
+      HIPCHK(hipStreamSynchronize(s));  // the last attempt's kernels still use the rows
+      const int32_t* fl = (const int32_t*)(h->pinned + kPinFlags);
+      const int32_t MR = std::max(h->MR, (int32_t)((fl[0] * 1.2 + 8) / 4 * 4 + 4));
+      const int32_t MA = std::max(h->MA, (int32_t)((fl[1] * 1.2 + 8) / 4 * 4 + 4));
+      ensure_lists(h, pp.N, MR, MA);
+      ensure_verlet(h, pp.N, std::max(h->V.MR, MR));
+      launch_fill_i32(h->flags, 8, 0, s);
+    }
     {
       Stage st(h, "neighbor_rows", s);
       launch_build_rows(b, h->V, h->L, s);
     }
-    int32_t* fl = (int32_t*)(h->pinned + kPinFlags);
-    HIPCHK(hipMemcpyAsync(fl, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    const int32_t* fl = (const int32_t*)(h->pinned + kPinFlags);
+    HIPCHK(hipMemcpyAsync(h->pinned + kPinFlags, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipEventRecord(h->flags_event, s));
+    eval();
+    HIPCHK(hipEventSynchronize(h->flags_event));
     if (fl[3]) throw Failure{NEP_E_INVALID_ARG, "an atom type is out of range"};
     if (fl[4]) throw Failure{NEP_E_NONFINITE, "positions contain NaN or Inf"};
     if (fl[0] == 0 && fl[1] == 0) {
       // without truncated rows every entry has its reverse entry
       if (fl[2]) throw Failure{NEP_E_HIP, "internal error: neighbour rows are not symmetric"};
       check_row_flag(fl[6]);
+      drain.armed = false;
       return;
     }
     const bool fixed = h->hp.max_nb_radial || h->hp.max_nb_angular;
@@ -959,16 +985,13 @@ void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, h
                     std::max(fl[0], h->MR), std::max(fl[1], h->MA));
       throw Failure{NEP_E_NEIGHBOR_OVERFLOW, msg};
     }
-    const int32_t MR = std::max(h->MR, (int32_t)((fl[0] * 1.2 + 8) / 4 * 4 + 4));
-    const int32_t MA = std::max(h->MA, (int32_t)((fl[1] * 1.2 + 8) / 4 * 4 + 4));
-    ensure_lists(h, pp.N, MR, MA);
-    ensure_verlet(h, pp.N, std::max(h->V.MR, MR));
   }
   throw Failure{NEP_E_NEIGHBOR_OVERFLOW, "neighbour rows kept overflowing"};
 }
 
+template <class Eval>
 void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, const int32_t* types_src,
-                     hipStream_t s) {
+                     hipStream_t s, Eval&& eval) {
   BuildArgs b = build_args(h, pp, pos_src, types_src, h->pos, h->types);
   b.check = h->flags;
   with_type_rows(h, b);
@@ -976,7 +999,12 @@ void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, c
     Stage st(h, "order_atoms", s);
     launch_order_atoms(b, s);
   }
-  build_rows_checked(h, pp, b, s);
+  build_rows_checked(h, pp, b, s, eval);
+}
+
+void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, const int32_t* types_src,
+                     hipStream_t s) {
+  order_and_build(h, pp, pos_src, types_src, s, [] {});
 }
 
 // Kernel shape of a call.  A quad of lanes per atom uses the lanes best (a row
@@ -1000,12 +1028,13 @@ const Tuning& pick_shape(nep_handle* h, const Prepared& pp) {
 
 // Descriptors, network, partial forces and the force gather; the per-atom
 // virial only when `virial` (MD steps without a thermo row skip it).
-// `filtered`: the rows come from skin_filter.
+// `filtered`: the rows come from skin_filter; `unchecked`: their flags have not been read.
 void forces(nep_handle* h, const Prepared& pp, hipStream_t s, const DevModel* model = nullptr,
-            bool virial = true, const MDArgs* kick = nullptr, bool filtered = false) {
+            bool virial = true, const MDArgs* kick = nullptr, bool filtered = false, bool unchecked = false) {
   const Tuning& t = pick_shape(h, pp);
   EvalArgs a = eval_args(h, pp, model ? *model : h->M);
   a.quads = t.quads;
+  if (unchecked) a.flags = h->flags;
   if (filtered && rev_in_candidates(pp.N, pp.batch)) {
     a.fmap = h->V.fmap;
     a.rev_err = h->flags + 2;
@@ -1102,12 +1131,11 @@ int compute_impl(nep_handle* h, int64_t N, const double* d_pos, const int32_t* d
                  const int32_t* pbc, double* d_energy, double* d_force, double* d_virial, double* d_totals,
                  hipStream_t s) {
   Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
-  order_and_build(h, pp, d_pos, d_types, s);
-  forces(h, pp, s);
+  order_and_build(h, pp, d_pos, d_types, s, [&] { forces(h, pp, s, nullptr, true, nullptr, false, true); });
   EvalArgs a = eval_args(h, pp, h->M);
   {
     Stage st(h, "outputs", s);
-    launch_scatter_outputs(a, h->perm, d_energy, d_force, d_virial, s);
+    if (d_energy || d_force || d_virial) launch_scatter_outputs(a, h->perm, d_energy, d_force, d_virial, s);
     if (d_totals) launch_totals(h->U, h->W, N, h->partial, num_partials(N), d_totals, s);
   }
   return NEP_OK;
@@ -1466,8 +1494,7 @@ void server_tick(nep_server* sv) {
   }
   launch_srv_kick_drift(N, b.pos, b.vel, b.F, b.hdm, b.dta, b.move, s);
   Prepared pp = prepare_batch(h, S, offs.data(), boxes.data(), pbcs.data(), h->hp.rc_radial, false, true, s);
-  order_and_build(h, pp, b.pos, b.types, s);
-  forces(h, pp, s);
+  order_and_build(h, pp, b.pos, b.types, s, [&] { forces(h, pp, s, nullptr, true, nullptr, false, true); });
   EvalArgs a = eval_args(h, pp, h->M);
   launch_scatter_outputs(a, h->perm, b.E, b.F, b.W, s);
   {
@@ -2098,10 +2125,12 @@ int nep_descriptors(nep_handle* h, int64_t N, const double* pos, const int32_t* 
       HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
       HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     }
-    order_and_build(h, pp, d_pos, d_types, s);
-    EvalArgs a = eval_args(h, pp, h->M);
-    a.quads = pick_shape(h, pp).quads;
-    if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
+    order_and_build(h, pp, d_pos, d_types, s, [&] {
+      EvalArgs a = eval_args(h, pp, h->M);
+      a.flags = h->flags;
+      a.quads = pick_shape(h, pp).quads;
+      if (!launch_descriptor(a, s)) throw Failure{NEP_E_UNSUPPORTED, "no descriptor kernel for this shape"};
+    });
     if (!io) {
       d_q = nullptr;
       dev_alloc(d_q, (size_t)N * h->nd);

@@ -25,6 +25,7 @@ namespace nep {
 
 template <int NT, int L, bool BATCH, int Q, int SH>
 __global__ void __launch_bounds__(kBlock, 2) k_descriptor(EvalArgs a, StructInfo st0) {
+  if (rows_refused(a)) return;
   constexpr int NB = num_poly(L), NBT = (NB + 3) / 4;
   using Sh = BasisShape<SH>;
   constexpr int KT = SH ? (Sh::KR + 3) / 4 : kMaxBasis / 4;  // basis tiles of F

@@ -53,6 +53,7 @@ __global__ void __launch_bounds__(kBlock, NT * num_poly(L) <= 72 ? 3 : 2) k_part
   constexpr int kAtoms = 64 / (4 * Q);  // atoms of a wave
   using Sh = BasisShape<SH>;
   extern __shared__ float4 lds_v4[];  // 16-byte aligned base
+  if (rows_refused(a)) return;
   float* sR = reinterpret_cast<float*>(lds_v4);
   const DevModel& M = a.M;
   const int T = M.T;
@@ -339,6 +340,7 @@ bool launch_partial_forces(const EvalArgs& a, hipStream_t s) {
 // VIRIAL = false leaves W untouched (MD steps without a thermo row).
 template <bool BATCH, bool VIRIAL, bool CAND, int G>
 __global__ void __launch_bounds__(kBlock) k_gather(EvalArgs a, StructInfo st0) {
+  if (rows_refused(a)) return;
   const int64_t N = a.N;
   const int sub = threadIdx.x & (G - 1);
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;

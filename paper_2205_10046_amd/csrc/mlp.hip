@@ -62,6 +62,7 @@ __device__ __forceinline__ void bf16x4_from_bits(uint2 u, v8bf& r, int off) {
 
 template <int NNB, bool BF16>
 __global__ void __launch_bounds__(256) k_mlp(EvalArgs a) {
+  if (rows_refused(a)) return;
   const DevModel& M = a.M;
   const int lane = threadIdx.x & 63;
   const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
@@ -369,6 +370,7 @@ __device__ __forceinline__ void stage_weights(const DevModel& M, int net, int ti
 template <int NNB, bool BF16>
 __global__ void __launch_bounds__(256, NNB <= 4 ? 4 : 1) k_mlp_lds(EvalArgs a, int32_t groups_per_block) {
   extern __shared__ float4 mlp_lds[];
+  if (rows_refused(a)) return;
   const DevModel& M = a.M;
   const int64_t n_groups = a.rows_len / kRowGroup;
   const int64_t g_begin = (int64_t)blockIdx.x * groups_per_block;

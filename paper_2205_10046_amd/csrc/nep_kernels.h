@@ -55,6 +55,9 @@ struct EvalArgs {
   // entry and fmap [MV][N] the exact position of every candidate (NULL: L.revR is that)
   const int32_t* fmap;
   int32_t* rev_err;           // set when a candidate has none
+  // flags of rows the host has not checked yet (NULL: checked): the evaluation kernels
+  // index their buffers through the rows, so they do nothing when one is set
+  const int32_t* flags;
   DevModel M;
   float* q;                   // [N][NDp]
   float* fp;                  // [N][NDp]
@@ -77,6 +80,14 @@ struct EvalArgs {
   int32_t batch;              // several structures: geometry from structs[sid]
   StructInfo st0;             // the geometry when batch == 0
 };
+
+// Whether the rows of a call may not be evaluated: overflowed [0] [1], unsymmetric
+// [2], a species [3] or a position [4] that is refused, a broken invariant [6].
+__device__ __forceinline__ bool rows_refused(const EvalArgs& a) {
+  if (!a.flags) return false;
+  const int32_t* f = a.flags;
+  return (f[0] | f[1] | f[2] | f[3] | f[4] | f[6]) != 0;
+}
 
 // neighbor.hip
 void launch_fill_i32(int32_t* a, int64_t n, int32_t v, hipStream_t s);
