@@ -155,16 +155,16 @@ __global__ void __launch_bounds__(kBlock, 2) k_descriptor(EvalArgs a, StructInfo
       const int t = t_first + X;
       if (t >= T) return;
       const float* c = sR + (ti * T + t) * KR * WR + min(4 * s, WR - 4);
-#pragma unroll
-      for (int k = 0; k < 4 * KT; ++k) {
-        if (k >= KR) break;
+      static_for<0, 4 * KT>([&](auto kk) __attribute__((always_inline)) {
+        constexpr int k = decltype(kk)::value;
+        if (k >= KR) return;
         const float Ftk = quad_bcast<X>(F[k / 4][k % 4]);
         const float4 c4 = *reinterpret_cast<const float4*>(c + k * WR);
         qr[0] += c4.x * Ftk;
         qr[1] += c4.y * Ftk;
         qr[2] += c4.z * Ftk;
         qr[3] += c4.w * Ftk;
-      }
+      });
     });
   };
   contract_radial(0);
