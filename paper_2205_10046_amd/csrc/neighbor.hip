@@ -736,12 +736,14 @@ __global__ void __launch_bounds__(kBlock) k_reverse_exact(
   if (i >= N) return;
   const int32_t* __restrict__ nl = L.nlR;
   const uint16_t* __restrict__ cd = L.cdR;
-  const int nn = L.nnR[i], na = L.nnA[i];
-  if (nn > L.MR) return;  // overflow: reported by the builder
+  // a row that overflowed (reported by the builder) is truncated, and so are its partners': an
+  // MD step evaluates it before the host knows, so its entries need a position in bounds too
+  const int all = L.nnR[i], part = L.nnA[i];
+  const int nn = min(all, L.MR), na = min(part, nn);
   const StructInfo& st = structs[sid[i]];
   const bool images = st.mode == kModeImages;
   const int64_t s_lo = st.start, s_hi = st.start + st.count;
-  int32_t b = na < 0 || nn < 0 || na > nn ? 1 : 0;
+  int32_t b = part < 0 || all < 0 || part > all ? 1 : 0;
   bool lost = false;
   double xi = 0.0, yi = 0.0, zi = 0.0;
   if (DISP) {

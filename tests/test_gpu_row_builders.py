@@ -99,3 +99,23 @@ def test_rows_filtered_from_candidates_give_the_same_steps(name, many):
     err = np.abs(out[0] - out[1]).max()
     print(f"[rows] {name} x{pos.shape[1] // n} with a skin: {err:.1e}", flush=True)
     assert np.isfinite(out[0]).all() and err < 2e-6
+
+
+def test_rows_that_outgrow_their_capacity_during_a_run():
+    """216 carbon atoms of a random model contract: their longest radial row passes the
+    60 slots of the first capacity near step 460, in the middle of a chunk of
+    steps, which is then evaluated on truncated rows and replayed on longer ones.
+    A handle whose rows are long from the start gives the same bits."""
+    h = synth.WORKLOADS["diamond216"]
+    pos, types, box = synth.diamond216()
+    m = np.array(synth.MASSES["diamond216"])
+    vel = synth.maxwell_velocities(m[types], 300.0)
+    out = []
+    for grown in (False, True):
+        handle = nep.Handle(h, synth.random_params(O.num_params(h), seed=synth.SEED_WEIGHTS))
+        if grown:
+            handle.neighbors(pos * 0.6, box * 0.6, 0, cap=512)
+        out.append(handle.md_run(pos, vel, types, m, box, 1.0, 520, 0))
+        handle.close()
+    assert max(len(j) for j, _ in O.pairs(out[0][0], box, h["rc_radial"])) > 60
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
