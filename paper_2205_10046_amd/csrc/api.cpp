@@ -321,6 +321,17 @@ struct Tuning {
 
 }  // namespace
 
+// A further branch of a population's graph: the buffers that a parameter set's
+// pass writes, its capture stream and the event of its end, see ensure_branches().
+constexpr int kMaxBranches = 4;
+
+struct Branch {
+  hipStream_t stream = nullptr;
+  hipEvent_t done = nullptr;
+  float *q = nullptr, *fp = nullptr, *U = nullptr, *sums = nullptr, *F = nullptr, *W = nullptr;
+  float4* P = nullptr;
+};
+
 struct nep_handle {
   nep_hparams hp{};
   int device = 0;
@@ -359,6 +370,8 @@ struct nep_handle {
   hipGraphExec_t md_exec = nullptr;
   std::vector<unsigned char> md_key;
   hipStream_t md_stream = nullptr;  // capture/replay stream for null-stream callers
+  Branch branch[kMaxBranches - 1];  // next to the handle's own stream and buffers
+  hipEvent_t branch_fork = nullptr;
   double* ens_state = nullptr;      // ensemble state, its chunk save and the saved cell
   double* ens_partial = nullptr;    // ensemble reduction partials
   int64_t ens_partial_cap = 0;
@@ -439,6 +452,14 @@ struct nep_handle {
     pop_tables_cap = 0;
     if (md_stream) (void)hipStreamDestroy(md_stream);
     md_stream = nullptr;
+    for (Branch& b : branch) {
+      if (b.stream) (void)hipStreamDestroy(b.stream);
+      if (b.done) (void)hipEventDestroy(b.done);
+      b.stream = nullptr;
+      b.done = nullptr;
+    }
+    if (branch_fork) (void)hipEventDestroy(branch_fork);
+    branch_fork = nullptr;
     if (pinned) (void)hipHostFree(pinned);
     pinned = nullptr;
     if (tab_event) (void)hipEventSynchronize(tab_event);
@@ -493,7 +514,20 @@ struct nep_handle {
     V = Lists{};
   }
 
+  void free_branches() {
+    for (Branch& b : branch) {
+      dev_free(b.q); dev_free(b.fp); dev_free(b.U); dev_free(b.sums);
+      dev_free(b.F); dev_free(b.W); dev_free(b.P);
+    }
+  }
+
+  void swap_buffers(Branch& b) {
+    std::swap(q, b.q); std::swap(fp, b.fp); std::swap(U, b.U); std::swap(sums, b.sums);
+    std::swap(F, b.F); std::swap(W, b.W); std::swap(P, b.P);
+  }
+
   void free_lists() {
+    free_branches();  // sized like the rows and the atoms' buffers, which go with them
     dev_free(L.nnR); dev_free(L.nlR); dev_free(L.cdR); dev_free(L.revR);
     dev_free(L.nnA);
     dev_free(P);
@@ -1141,6 +1175,51 @@ int compute_impl(nep_handle* h, int64_t N, const double* d_pos, const int32_t* d
   return NEP_OK;
 }
 
+// Branches of a population's graph.  A parameter set's kernels leave room on the
+// chip (a wave takes 16 atoms: 26,128 are fewer than two waves per SIMD) and gaps
+// between them, so the passes of several sets run side by side, each with its
+// own buffers.  Us per set of the 3-species training model, with 1, 2, 3 and 4
+// branches: 62, 50, 39, 37 for 244 atoms; 76, 58, 49, 47 for 6,532; 136, 103, 97,
+// 94 for 26,128; 219, 181, 175, 169 for 52,256; 472 and 407 for 130,640 with 1 and 2.
+// The buffers take about 3 KB per atom and branch: two beyond 65,536 atoms, where
+// more give little, and one beyond 262,144.
+int population_branches(int64_t N, int32_t P) {
+  const int most = N < 65536 ? 4 : (N < 262144 ? 2 : 1);
+  return std::min<int>(P, most);
+}
+
+// The branches next to the handle's own, as many of n - 1 as are to be had.
+int ensure_branches(nep_handle* h, int n) {
+  if (n < 2) return 1;
+  if (!h->branch_fork && hipEventCreateWithFlags(&h->branch_fork, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    h->branch_fork = nullptr;
+    return 1;
+  }
+  const size_t c = (size_t)h->capN;
+  const DevModel& M = h->M;
+  for (int k = 0; k + 1 < n; ++k) {
+    Branch& b = h->branch[k];
+    if ((!b.stream && hipStreamCreateWithFlags(&b.stream, hipStreamNonBlocking) != hipSuccess) ||
+        (!b.done && hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess)) {
+      (void)hipGetLastError();
+      return k + 1;
+    }
+    if (b.P) continue;
+    try {
+      dev_alloc(b.q, c * M.NDp); dev_alloc(b.fp, c * M.NDp);
+      dev_alloc(b.U, c); dev_alloc(b.sums, (size_t)sums_floats(M) * c);
+      dev_alloc(b.F, 3 * c); dev_alloc(b.W, 9 * c);
+      dev_alloc(b.P, (size_t)h->MR * c);
+    } catch (const Failure&) {
+      dev_free(b.q); dev_free(b.fp); dev_free(b.U); dev_free(b.sums);
+      dev_free(b.F); dev_free(b.W); dev_free(b.P);
+      return k + 1;
+    }
+  }
+  return n;
+}
+
 // Batch of structures x parameter sets (device pointers).  Rows are built once
 // and shared by every parameter set (or reused from the previous batch call
 // when the caller says the structures are the same); the per-set passes are
@@ -1203,6 +1282,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     h->batch_cells = pp.n_cells;
   }
   pick_shape(h, pp);
+  const int branches = ensure_branches(h, population_branches(N, P));
   // everything the captured kernels hold by value or by address
   std::vector<unsigned char> key;
   auto put = [&](const void* p, size_t n) {
@@ -1214,6 +1294,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
   put(&S, sizeof S);
   put(&N, sizeof N);
   put(&P, sizeof P);
+  put(&branches, sizeof branches);
   const void* ptrs[6] = {d_params, d_energy, d_force, d_virial, d_totals, params};
   put(ptrs, sizeof ptrs);
   const bool timing = h->timing;
@@ -1229,13 +1310,30 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     try {
       HIPCHK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
       if (d_params) launch_model_tables(d_params, (int64_t)n_params(h->hp), P, TL, h->pop_tables, TL.set_bytes, cs);
+      if (branches > 1) HIPCHK(hipEventRecord(h->branch_fork, cs));
+      for (int k = 0; k + 1 < branches; ++k) HIPCHK(hipStreamWaitEvent(h->branch[k].stream, h->branch_fork, 0));
       for (int32_t p = 0; p < P; ++p) {
-        forces(h, pp, cs, &models[p]);
+        struct Swap {  // a branch's buffers are the handle's while its sets are captured
+          nep_handle* h;
+          Branch* b;
+          Swap(nep_handle* h, Branch* b) : h(h), b(b) {
+            if (b) h->swap_buffers(*b);
+          }
+          ~Swap() {
+            if (b) h->swap_buffers(*b);
+          }
+        } swap(h, p % branches ? &h->branch[p % branches - 1] : nullptr);
+        hipStream_t const ps = swap.b ? swap.b->stream : cs;
+        forces(h, pp, ps, &models[p]);
         EvalArgs a = eval_args(h, pp, models[p]);
         launch_scatter_outputs(a, h->perm, d_energy ? d_energy + (size_t)p * N : nullptr,
                                d_force ? d_force + (size_t)p * 3 * N : nullptr,
-                               d_virial ? d_virial + (size_t)p * 9 * N : nullptr, cs);
-        if (d_totals) launch_struct_totals(h->U, h->W, N, h->structs, S, d_totals + (size_t)p * S * 10, cs);
+                               d_virial ? d_virial + (size_t)p * 9 * N : nullptr, ps);
+        if (d_totals) launch_struct_totals(h->U, h->W, N, h->structs, S, d_totals + (size_t)p * S * 10, ps);
+      }
+      for (int k = 0; k + 1 < branches; ++k) {
+        HIPCHK(hipEventRecord(h->branch[k].done, h->branch[k].stream));
+        HIPCHK(hipStreamWaitEvent(cs, h->branch[k].done, 0));
       }
       HIPCHK(hipStreamEndCapture(cs, &h->batch_graph));
       HIPCHK(hipGraphInstantiate(&h->batch_exec, h->batch_graph, nullptr, nullptr, 0));
