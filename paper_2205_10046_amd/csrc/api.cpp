@@ -1856,7 +1856,7 @@ int nep_compute(nep_handle* h, int64_t N, const double* pos, const int32_t* type
                     *const dT = dW + (virial ? 9 * N : 0);
       compute_impl(h, N, d_pos, d_types, box, pbc, energy ? dE : nullptr, force ? dF : nullptr, virial ? dW : nullptr,
                    totals ? dT : nullptr, s);
-      HIPCHK(hipMemcpyAsync(h->io_host, at, n_out * sizeof(double), hipMemcpyDeviceToHost, s));
+      if (n_out) HIPCHK(hipMemcpyAsync(h->io_host, at, n_out * sizeof(double), hipMemcpyDeviceToHost, s));
       HIPCHK(hipStreamSynchronize(s));
       const double* r = (const double*)h->io_host;
       if (energy) std::memcpy(energy, r, N * sizeof(double));
