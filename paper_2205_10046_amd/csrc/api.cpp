@@ -840,7 +840,6 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.rcR2 = h->hp.rc_radial * h->hp.rc_radial;
   b.rcA2 = h->hp.rc_angular * h->hp.rc_angular;
   b.overflow = h->flags;
-  b.disp = pp.batch ? h->disp : nullptr;
   b.n_struct = (int32_t)pp.sts.size();
   b.n_types = h->M.T;
   b.per_type = h->hp.nn_per_type;
@@ -995,7 +994,7 @@ void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, h
     }
     {
       Stage st(h, "neighbor_rows", s);
-      launch_build_rows(b, h->V, h->L, s);
+      launch_build_rows(b, h->V, h->L, pp.batch ? h->disp : nullptr, s);
     }
     const int32_t* fl = (const int32_t*)(h->pinned + kPinFlags);
     HIPCHK(hipMemcpyAsync(h->pinned + kPinFlags, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -2308,7 +2307,7 @@ void skin_rebuild(nep_handle* h, const Prepared& pp, double rl, const int32_t* g
 
 void skin_filter(nep_handle* h, const Prepared& pp, hipStream_t s) {
   BuildArgs bf = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
-  launch_filter_rows(bf, pp.geo.st, pp.batch, h->V, h->L, s);
+  launch_filter_rows(bf, pp.geo.st, pp.batch, h->V, h->L, pp.batch ? h->disp : nullptr, s);
 }
 
 // Grow whichever rows overflowed (flags [0] radial, [1] angular, [5]
@@ -2837,7 +2836,7 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       {
         Stage st(h, "neighbor_rows", s);
         BuildArgs b2 = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
-        launch_build_rows(b2, h->V, h->L, s);
+        launch_build_rows(b2, h->V, h->L, nullptr, s);
       }
       forces(h, pp, s, nullptr, thermo_every > 0 && step % thermo_every == 0);
       md.pos = h->pos;

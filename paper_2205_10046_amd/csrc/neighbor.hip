@@ -979,18 +979,18 @@ static void launch_members(const BuildArgs& b, const Lists& V, const Lists& L, h
 }
 
 template <bool DISP, int G>
-static void launch_reverse_exact(const BuildArgs& b, const Lists& L, hipStream_t s) {
+static void launch_reverse_exact(const BuildArgs& b, const Lists& L, float4* disp, hipStream_t s) {
   hipLaunchKernelGGL((k_reverse_exact<DISP, G>), grid_for(b.N * G), dim3(kBlock), 0, s, b.N, L, b.pos, b.types, b.sid,
-                     b.structs, b.disp, b.overflow + 2, b.overflow + 6);
+                     b.structs, disp, b.overflow + 2, b.overflow + 6);
 }
 
-void launch_build_rows(const BuildArgs& b0, const Lists& V, const Lists& L, hipStream_t s) {
+void launch_build_rows(const BuildArgs& b0, const Lists& V, const Lists& L, float4* disp, hipStream_t s) {
   BuildArgs b = b0;
   b.gate = nullptr;
   launch_members<true>(b, V, L, s);
   const bool wide = b.N < kFewAtoms;
-  if (b.disp) wide ? launch_reverse_exact<true, 16>(b, L, s) : launch_reverse_exact<true, 8>(b, L, s);
-  else wide ? launch_reverse_exact<false, 16>(b, L, s) : launch_reverse_exact<false, 8>(b, L, s);
+  if (disp) wide ? launch_reverse_exact<true, 16>(b, L, disp, s) : launch_reverse_exact<true, 8>(b, L, disp, s);
+  else wide ? launch_reverse_exact<false, 16>(b, L, disp, s) : launch_reverse_exact<false, 8>(b, L, disp, s);
 }
 
 void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate, hipStream_t s) {
@@ -1390,7 +1390,7 @@ bool rev_in_candidates(int64_t N, bool batch) { return !batch && N < kFewAtoms; 
 
 template <int G>
 static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V, const Lists& L,
-                            hipStream_t s) {
+                            float4* disp, hipStream_t s) {
   const dim3 grid = grid_for(b.N * G);
   if (batch)
     hipLaunchKernelGGL((k_filter_rows<true, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
@@ -1400,7 +1400,7 @@ static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batc
                        st0, V, b.rcR2, b.rcA2, L, b.overflow);
   if (batch)
     hipLaunchKernelGGL((k_reverse_from_candidates<true, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
-                       b.pos, b.types, b.sid, b.structs, b.disp, b.overflow + 2);
+                       b.pos, b.types, b.sid, b.structs, disp, b.overflow + 2);
   else if (!rev_in_candidates(b.N, batch))
     hipLaunchKernelGGL((k_reverse_from_candidates<false, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        (const double*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr,
@@ -1408,9 +1408,9 @@ static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batc
 }
 
 void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                        const Lists& L, hipStream_t s) {
-  if (b.N < kFewAtoms) launch_filter_g<16>(b, st0, batch, V, L, s);
-  else launch_filter_g<4>(b, st0, batch, V, L, s);
+                        const Lists& L, float4* disp, hipStream_t s) {
+  if (b.N < kFewAtoms) launch_filter_g<16>(b, st0, batch, V, L, disp, s);
+  else launch_filter_g<4>(b, st0, batch, V, L, disp, s);
 }
 
 // flag = any atom whose displacement since the last build, plus horizon

@@ -24,7 +24,6 @@ struct BuildArgs {
   int32_t* overflow;          // flags: [0] radial row, [1] angular row, [2] rev error,
                               // [5] candidate row overflow (max counts)
   const int32_t* gate;        // rebuild kernels run only when *gate != 0 (NULL: always)
-  float4* disp = nullptr;     // batches: displacement and species of every exact entry, [MR][N]
   int32_t wide_rows = 0;      // some structure has no cells: its rows come from k_build_rows_wide
   int32_t cell_rows = 0;      // some structure has cells: its rows come from k_build_rows_cells
   int32_t n_struct = 1;
@@ -96,8 +95,11 @@ void launch_assign_struct(const int64_t* offs, int32_t n_struct, int64_t N, int3
 // Internal order of the atoms and everything that follows from it.
 void launch_order_atoms(const BuildArgs& b, hipStream_t s);
 // Exact rows L at the cutoffs of b with their reverse index, every row
-// invariant checked (flags [2] and [6]); V's rows serve as scratch.
-void launch_build_rows(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s);
+// invariant checked (flags [2] and [6]); V's rows serve as scratch.  disp: the
+// displacement and species of every entry, [MR][N] (batches; NULL: not stored).
+// V, L and disp are the buffers that a call regrows when a row overflows, so
+// they are not part of b.
+void launch_build_rows(const BuildArgs& b, const Lists& V, const Lists& L, float4* disp, hipStream_t s);
 void launch_reverse(int64_t N, const Lists& L, int32_t* err, const int32_t* gate, hipStream_t s);
 // Sets bits of *bad when the exact rows break an invariant the evaluation
 // kernels rely on for in-bounds access (see neighbor.hip).  V: the candidates
@@ -114,7 +116,7 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
 // Whether launch_filter_rows leaves the candidates' reverse positions in L.revR.
 bool rev_in_candidates(int64_t N, bool batch);
 void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                        const Lists& L, hipStream_t s);
+                        const Lists& L, float4* disp, hipStream_t s);
 // flag = 1 if an atom moved more than allowed since the last build, or will
 // have once it moves `horizon` times its current speed further (vel given);
 // with mu_cum (box scaling since the build, NPT) the allowance shrinks to
