@@ -64,12 +64,20 @@ __host__ __device__ inline void split_code(uint16_t code, int& a, int& b, int& c
   c = (code & 15) - 8;
 }
 
+// Fractional offset s_k of a bond along cell vector k from column k of Hi.  The
+// image codes of a row count from rint(s), and an atom half a cell vector away
+// makes that a matter of the last bit: everyone who needs s takes this one
+// order of operations, with no contraction left to the compiler.
+__host__ __device__ inline double bond_fraction(const double* Hi_k, double Dx, double Dy, double Dz) {
+  return fma(Dz, Hi_k[6], fma(Dx, Hi_k[0], Dy * Hi_k[3]));
+}
+
 // Minimum-image offset n0 = -rint(s) of the fractional bond offset s along
 // each periodic cell vector (0 along open directions).
 // For a diagonal H the off-diagonal products are exact zeros, so the
 // diagonal-only forms below give the same bits as the general ones.
-__device__ inline void min_image(const StructInfo& st, double Dx, double Dy, double Dz,
-                                 int& n0, int& n1, int& n2) {
+__host__ __device__ inline void min_image(const StructInfo& st, double Dx, double Dy, double Dz,
+                                          int& n0, int& n1, int& n2) {
   n0 = n1 = n2 = 0;
   if (st.ortho) {
     if (st.pbc[0]) n0 = -(int)rint(Dx * st.Hi[0]);
@@ -77,17 +85,17 @@ __device__ inline void min_image(const StructInfo& st, double Dx, double Dy, dou
     if (st.pbc[2]) n2 = -(int)rint(Dz * st.Hi[8]);
     return;
   }
-  if (st.pbc[0]) n0 = -(int)rint(Dx * st.Hi[0] + Dy * st.Hi[3] + Dz * st.Hi[6]);
-  if (st.pbc[1]) n1 = -(int)rint(Dx * st.Hi[1] + Dy * st.Hi[4] + Dz * st.Hi[7]);
-  if (st.pbc[2]) n2 = -(int)rint(Dx * st.Hi[2] + Dy * st.Hi[5] + Dz * st.Hi[8]);
+  if (st.pbc[0]) n0 = -(int)rint(bond_fraction(st.Hi, Dx, Dy, Dz));
+  if (st.pbc[1]) n1 = -(int)rint(bond_fraction(st.Hi + 1, Dx, Dy, Dz));
+  if (st.pbc[2]) n2 = -(int)rint(bond_fraction(st.Hi + 2, Dx, Dy, Dz));
 }
 
 // d = (r_j - r_i) + ((n0 a + n1 b) + n2 c) with every product and sum rounded
 // separately (no fused multiply-add), so that neighbour membership decided
 // from |d|^2 is reproducible bit for bit.
-__device__ inline void image_disp(const StructInfo& st, double Dx, double Dy, double Dz,
-                                  int n0, int n1, int n2, double& dx, double& dy,
-                                  double& dz) {
+__host__ __device__ inline void image_disp(const StructInfo& st, double Dx, double Dy, double Dz,
+                                           int n0, int n1, int n2, double& dx, double& dy,
+                                           double& dz) {
 #pragma clang fp contract(off)
   const double a = (double)n0, b = (double)n1, c = (double)n2;
   if (st.ortho) {

@@ -102,12 +102,44 @@ __device__ __forceinline__ Basis make_basis(float r, float rc) {
 struct Frame {
   double H[9], Hi[9];
   bool images, ortho;
-  __device__ __forceinline__ explicit Frame(const StructInfo& st)
+  __host__ __device__ __forceinline__ explicit Frame(const StructInfo& st)
       : images(st.mode == kModeImages), ortho(st.ortho != 0) {
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
       H[k] = st.H[k];
       Hi[k] = st.pbc[k % 3] ? st.Hi[k] : 0.0;
+    }
+  }
+  // Displacement of an entry from the difference of the positions: the nearest
+  // image, min_image's to the bit, plus the offset of its code.  The fused
+  // multiply-adds of a diagonal cell round like image_disp's separate operations
+  // for offsets up to two cells, where the products are exact.
+  __host__ __device__ __forceinline__ void displacement(double Dx, double Dy, double Dz, uint16_t code, double& dx,
+                                                        double& dy, double& dz) const {
+    double n0, n1, n2;
+    if (ortho) {
+      n0 = rint(Dx * Hi[0]);
+      n1 = rint(Dy * Hi[4]);
+      n2 = rint(Dz * Hi[8]);
+    } else {
+      n0 = rint(bond_fraction(Hi, Dx, Dy, Dz));
+      n1 = rint(bond_fraction(Hi + 1, Dx, Dy, Dz));
+      n2 = rint(bond_fraction(Hi + 2, Dx, Dy, Dz));
+    }
+    if (images) {
+      int oa, ob, oc;
+      split_code(code, oa, ob, oc);
+      n0 -= (double)oa;
+      n1 -= (double)ob;
+      n2 -= (double)oc;
+    }
+    dx = fma(-n0, H[0], Dx);
+    dy = fma(-n1, H[4], Dy);
+    dz = fma(-n2, H[8], Dz);
+    if (!ortho) {
+      dx -= n1 * H[3] + n2 * H[6];
+      dy -= n0 * H[1] + n2 * H[7];
+      dz -= n0 * H[2] + n1 * H[5];
     }
   }
 };
@@ -118,9 +150,7 @@ struct Frame {
 // entry and its species; past the row the displacement is (1, 0, 0).
 // One structure: the index of entry k + 2 and the position and species of
 // entry k + 1 are in flight while entry k is computed; the displacement is the
-// float64 minimum image (offset -rint(s) plus the entry's image code) rounded
-// once; the fused multiply-adds round like the row builder's separate
-// operations for offsets up to two cells, where the products are exact.
+// float64 one of the frame rounded once.
 // A batch: rows come with their displacements and species (a.disp), one
 // 16-byte load per entry two steps ahead: every parameter set and both
 // kernels walk the same rows, and a lane then needs no structure.
@@ -169,28 +199,8 @@ __device__ __forceinline__ void walk_row(const EvalArgs& a, const Frame& fr, int
       pz = pos[2 * N + j0];
       t0 = a.types[j0];
       j1 = words(m + 2 * step, c1);
-      double n0 = Dx * fr.Hi[0], n1 = Dy * fr.Hi[4], n2 = Dz * fr.Hi[8];
-      if (!fr.ortho) {
-        n0 += Dy * fr.Hi[3] + Dz * fr.Hi[6];
-        n1 += Dx * fr.Hi[1] + Dz * fr.Hi[7];
-        n2 += Dx * fr.Hi[2] + Dy * fr.Hi[5];
-      }
-      n0 = rint(n0);
-      n1 = rint(n1);
-      n2 = rint(n2);
-      if (fr.images) {
-        int oa, ob, oc;
-        split_code(cc, oa, ob, oc);
-        n0 -= (double)oa;
-        n1 -= (double)ob;
-        n2 -= (double)oc;
-      }
-      double dx = fma(-n0, fr.H[0], Dx), dy = fma(-n1, fr.H[4], Dy), dz = fma(-n2, fr.H[8], Dz);
-      if (!fr.ortho) {
-        dx -= n1 * fr.H[3] + n2 * fr.H[6];
-        dy -= n0 * fr.H[1] + n2 * fr.H[7];
-        dz -= n0 * fr.H[2] + n1 * fr.H[5];
-      }
+      double dx, dy, dz;
+      fr.displacement(Dx, Dy, Dz, cc, dx, dy, dz);
       const bool in = m < nn;
       body(k, m, (int64_t)m * N + i, tc, in ? (float)dx : 1.f, in ? (float)dy : 0.f, in ? (float)dz : 0.f);
     }

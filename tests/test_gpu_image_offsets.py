@@ -1,0 +1,90 @@
+"""Perfect crystals in small cells that are not orthogonal: many atoms lie
+exactly half a cell vector apart, where the nearest image is a matter of the
+last bit and the image codes of the rows hold only for one way of rounding it.
+Whoever evaluates a row has to round it like the builder; then energies, forces,
+virials, descriptors, steps and elastic constants are the oracle's, to the
+bounds of the other float32 tests (1e-6 eV an atom, 1e-5 eV a site, 1e-4 eV/A,
+1e-4 eV, 1e-5 of a descriptor's range)."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2205_10046_amd import nep, synth
+
+pytestmark = pytest.mark.gpu
+
+HALF = 0.5 * (np.ones((3, 3)) - np.eye(3))
+# primitive vectors and basis in units of the cubic lattice constant, constant, repeats, shear
+CELLS = {
+    "fcc-2": (HALF, [[0, 0, 0]], 4.05, 2, 0.0),
+    "fcc-4": (HALF, [[0, 0, 0]], 4.05, 4, 0.0),
+    "bcc-4": (0.5 - np.eye(3), [[0, 0, 0]], 3.16, 4, 0.0),
+    "diamond-2": (HALF, [[0, 0, 0], [0.25] * 3], 5.43, 2, 0.0),
+    "fcc-sheared": (np.eye(3), [[0, 0, 0], *HALF], 4.05, 2, 0.01),
+    "diamond-sheared": (np.eye(3), [[0, 0, 0], *HALF, [0.25] * 3, *(np.array(HALF) + 0.25)], 5.43, 2, 0.01),
+}
+H = synth.hparams(2, 6.0, 5.0, 4, 4, 5, 5, 4, 2, 0, 16, 0)
+
+
+def _cell(name, origin):
+    vectors, basis, a, n, shear = CELLS[name]
+    at = np.stack(np.meshgrid(*[range(n)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    frac = (at @ vectors)[:, None] + np.array(basis, float)[None]
+    deform = np.eye(3) + shear * np.eye(3)[[1, 2, 0]]
+    pos = (frac.reshape(-1, 3) + origin) @ deform * a
+    box = n * vectors @ deform * a
+    if np.linalg.det(box) < 0:
+        box = box[[1, 0, 2]]
+    types = np.arange(pos.shape[0], dtype=np.int32) % 2
+    return np.ascontiguousarray(pos.T), types, np.ascontiguousarray(box).reshape(9)
+
+
+@pytest.mark.parametrize("origin", [0.0, 0.137])
+@pytest.mark.parametrize("name", CELLS)
+def test_perfect_cells_match_the_oracle(name, origin):
+    pos, types, box = _cell(name, origin)
+    n = pos.shape[1]
+    p = synth.random_params(O.num_params(H), seed=8)
+    ref = O.evaluate(H, p, pos, types, box)
+    handle = nep.Handle(H, p)
+    got = handle.compute(pos, types, box)
+    err = [np.abs(got[k] - ref[k]).max() for k in ("U", "F", "W")]
+    q = O.descriptors(H, p, pos, types, box)
+    dq = (np.abs(handle.descriptors(pos, types, box) - q) / (np.abs(q).max(axis=0) + 1e-3)).max()
+    vel = np.random.default_rng(2).normal(0, 2e-3, pos.shape)
+    heat = np.abs(handle.heat_current(pos, vel, types, box)[0] - O.heat_current(H, p, pos, vel, types, box)[0]).max()
+    print(f"[offsets] {name}+{origin} N={n}: |dU| {err[0]:.1e} |dF| {err[1]:.1e} |dW| {err[2]:.1e} |dq| {dq:.1e} "
+          f"|dJ| {heat:.1e}", flush=True)
+    assert abs(got["U"].sum() - ref["U"].sum()) / n <= 1e-6 and err[0] <= 1e-5 and err[1] <= 1e-4 and err[2] <= 1e-4
+    assert dq < 1e-5
+    assert heat <= 1e-4 * 3 * np.abs(vel).max()
+    handle.close()
+
+
+@pytest.mark.parametrize("name", CELLS)
+def test_perfect_cells_take_the_oracles_steps(name):
+    """Forces within 1e-4 eV/A, so positions of mass 12 after 4 steps of 1 fs within
+    1e-4 x 9.65e-3 / 12 x 4^2 / 2 < 1e-6 A."""
+    pos, types, box = _cell(name, 0.0)
+    p = synth.random_params(O.num_params(H), seed=8)
+    vel = np.random.default_rng(3).normal(0, 2e-3, pos.shape)
+    want = O.md_nve(H, p, pos, vel, types, [12.0, 12.0], box, 1.0, 4, 0)[0]
+    handle = nep.Handle(H, p)
+    got = handle.md_run(pos, vel, types, [12.0, 12.0], box, 1.0, 4, 0)[0]
+    print(f"[offsets] {name}: {np.abs(got - want).max():.1e} A", flush=True)
+    assert np.abs(got - want).max() < 1e-6
+    handle.close()
+
+
+@pytest.mark.parametrize("kind,a", [("fcc", 4.05), ("diamond", 5.43)])
+def test_elastic_constants_of_a_small_cell(kind, a):
+    """Cells of two lattice constants, whose shear strain makes exactly such a cell;
+    bounds as for the wider ones: strains of 1 % magnify the float32 energies."""
+    h = synth.hparams(1, 6.0, 5.0, 4, 4, 5, 5, 4, 2, 0, 16, 0)
+    p = synth.random_params(O.num_params(h), seed=3)
+    pos, types, box = synth.lattice(kind, 2, a, 0.0, 1)
+    handle = nep.Handle(h, p)
+    got, ref = handle.elastic_cubic(pos, types, box, 0.01), O.elastic_cubic(h, p, pos, types, box, 0.01)
+    print(f"[offsets] elastic {kind}: {got} (oracle {ref})", flush=True)
+    np.testing.assert_allclose(got, ref, rtol=2e-3, atol=0.05)
+    handle.close()
