@@ -372,7 +372,7 @@ struct nep_handle {
   hipStream_t md_stream = nullptr;  // capture/replay stream for null-stream callers
   Branch branch[kMaxBranches - 1];  // next to the handle's own stream and buffers
   hipEvent_t branch_fork = nullptr;
-  double* ens_state = nullptr;      // ensemble state, its chunk save and the saved cell
+  double* ens_state = nullptr;      // ensemble state, its chunk save, the saved cell and the last rebuild's
   double* ens_partial = nullptr;    // ensemble reduction partials
   int64_t ens_partial_cap = 0;
   DevModel& M = main.M;
@@ -2282,6 +2282,9 @@ int nep_latent(nep_handle* h, int64_t N, const double* pos, const int32_t* types
 
 namespace {
 
+// The structure as it was when the candidate rows were built (NPT: the cell changes).
+StructInfo* cell_at_rebuild(nep_handle* h) { return (StructInfo*)((unsigned char*)h->ens_state + 1536); }
+
 // Rebuild now from the current internal state: re-sort into cell order
 // (velocities and caller indices follow), remember the positions, and build
 // the candidate rows.  gate = NULL runs unconditionally.
@@ -2298,7 +2301,8 @@ void skin_rebuild(nep_handle* h, const Prepared& pp, double rl, const int32_t* g
   with_type_rows(h, br);
   launch_order_atoms(br, s);
   launch_commit_rebuild(N, h->pos2, h->vel2, h->types2, h->ext_id2, h->pos, h->vel, h->types,
-                        h->ext_id, h->pos_ref, gate, s, mu_cum, h->flags + kFlagRebuilds);
+                        h->ext_id, h->pos_ref, gate, s, mu_cum, h->flags + kFlagRebuilds, h->structs,
+                        pp.batch ? cell_at_rebuild(h) : nullptr);
   BuildArgs bv = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
   bv.rcR2 = rl * rl;
   bv.gate = gate;
@@ -2307,7 +2311,8 @@ void skin_rebuild(nep_handle* h, const Prepared& pp, double rl, const int32_t* g
 
 void skin_filter(nep_handle* h, const Prepared& pp, hipStream_t s) {
   BuildArgs bf = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
-  launch_filter_rows(bf, pp.geo.st, pp.batch, h->V, h->L, pp.batch ? h->disp : nullptr, s);
+  launch_filter_rows(bf, pp.geo.st, pp.batch, h->pos_ref, pp.batch ? cell_at_rebuild(h) : nullptr, h->V, h->L,
+                     pp.batch ? h->disp : nullptr, s);
 }
 
 // Grow whichever rows overflowed (flags [0] radial, [1] angular, [5]
@@ -2371,8 +2376,8 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
   EnsState* est = nullptr;
   double* mu_cum = nullptr;
   if (ens) {
-    // [state][saved state][saved structure 0], 256-byte aligned parts
-    if (!h->ens_state) dev_alloc(h->ens_state, 3 * 512 / sizeof(double));
+    // [state][saved state][saved structure 0][structure 0 at the last rebuild], 512 bytes each
+    if (!h->ens_state) dev_alloc(h->ens_state, 4 * 512 / sizeof(double));
     static_assert(sizeof(StructInfo) <= 512, "staging slot");
     const int64_t need = std::max<int64_t>(ens_partials(N), div_up(N, 256) + 1) + 1;
     if (need > h->ens_partial_cap) {

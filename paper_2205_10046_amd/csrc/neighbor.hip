@@ -242,10 +242,12 @@ __global__ void k_commit_rebuild(int64_t N, const double* __restrict__ pos2,
                                  const int32_t* __restrict__ ext2, double* __restrict__ pos,
                                  double* __restrict__ vel, int32_t* __restrict__ types,
                                  int32_t* __restrict__ ext, double* __restrict__ pos_ref,
-                                 const int32_t* gate, double* mu_cum, int32_t* count) {
+                                 const int32_t* gate, double* mu_cum, int32_t* count,
+                                 const StructInfo* __restrict__ st, StructInfo* __restrict__ st_ref) {
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= N || gated_off(gate)) return;
   if (k == 0 && mu_cum) *mu_cum = 1.0;  // the reference positions are the current ones
+  if (k == 0 && st_ref) *st_ref = *st;  // and so is the reference cell
   if (k == 0 && count) atomicAdd(count, 1);  // rebuilds done
   for (int c = 0; c < 3; ++c) {
     const double x = pos2[c * N + k];
@@ -936,9 +938,9 @@ void launch_assign_struct(const int64_t* offs, int32_t n_struct, int64_t N, int3
 void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, const int32_t* types2,
                            const int32_t* ext2, double* pos, double* vel, int32_t* types, int32_t* ext,
                            double* pos_ref, const int32_t* gate, hipStream_t s, double* mu_cum,
-                           int32_t* count) {
+                           int32_t* count, const StructInfo* st, StructInfo* st_ref) {
   hipLaunchKernelGGL(k_commit_rebuild, grid_for(N), dim3(kBlock), 0, s, N, pos2, vel2, types2, ext2,
-                     pos, vel, types, ext, pos_ref, gate, mu_cum, count);
+                     pos, vel, types, ext, pos_ref, gate, mu_cum, count, st, st_ref);
 }
 
 // Below this many atoms the row kernels give an atom more lanes: a whole wave
@@ -1021,13 +1023,36 @@ void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s) {
 // register bit masks; pass 2 goes through the candidates in order, and
 // counts over wave ballots of the class flags give each member its exact position.
 // The rows are the same as those of a single sequential pass.
+// With images a candidate's code counts from the nearest image at the build, and
+// an atom near half a cell vector has another one as soon as it moves: the
+// entry is the same image all the same, so its offset comes from the reference
+// positions (and cell, st_ref, where the cell changes), and the exact entry's code
+// counts from the nearest image now, which its readers take.
 constexpr int kFilterChunk = 4;
+
+struct ImageOffset {
+  int n[3];
+};
+
+// Offset of the candidate of code `code`, from the difference of the reference positions.
+__device__ __forceinline__ ImageOffset offset_at_build(const StructInfo& st, const double* __restrict__ ref, int64_t N,
+                                                       int64_t i, int64_t j, uint16_t code) {
+  ImageOffset o;
+  int a, b, c;
+  min_image(st, ref[j] - ref[i], ref[N + j] - ref[N + i], ref[2 * N + j] - ref[2 * N + i], o.n[0], o.n[1], o.n[2]);
+  split_code(code, a, b, c);
+  o.n[0] += a;
+  o.n[1] += b;
+  o.n[2] += c;
+  return o;
+}
 
 template <bool BATCH, int G>
 __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict__ pos, int64_t N,
                                                         const int32_t* __restrict__ sid,
                                                         const StructInfo* __restrict__ structs,
-                                                        StructInfo st0, Lists V, double rcR2,
+                                                        StructInfo st0, const double* __restrict__ ref,
+                                                        const StructInfo* __restrict__ st_ref, Lists V, double rcR2,
                                                         double rcA2, Lists L,
                                                         int32_t* __restrict__ overflow) {
   constexpr int U = kFilterChunk;
@@ -1036,6 +1061,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
   const int64_t i = (xcd_block() * blockDim.x + threadIdx.x) / G;
   if (i >= N) return;  // the lanes of an atom leave together
   const StructInfo& st = BATCH ? structs[sid[i]] : st0;
+  const StructInfo& st_built = BATCH ? *st_ref : st0;
   const int32_t* __restrict__ vnl = V.nlR;
   const uint16_t* __restrict__ vcd = V.cdR;
   const int32_t* __restrict__ vrev = V.revR;
@@ -1096,13 +1122,13 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
         Dz = pz[u] - zi;
       }
       int n0, n1, n2;
-      min_image(st, Dx, Dy, Dz, n0, n1, n2);
-      if (code[u] != kCodeCenter) {
-        int oa, ob, oc;
-        split_code(code[u], oa, ob, oc);
-        n0 += oa;
-        n1 += ob;
-        n2 += oc;
+      if (images) {
+        const ImageOffset o = offset_at_build(st_built, ref, N, i, j[u], code[u]);
+        n0 = o.n[0];
+        n1 = o.n[1];
+        n2 = o.n[2];
+      } else {
+        min_image(st, Dx, Dy, Dz, n0, n1, n2);
       }
       double dx, dy, dz;
       image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
@@ -1154,7 +1180,12 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
       if (cq[u] != -1) {
         jq[u] = vnl[e];
         rq[u] = vrev[e];
-        if (images) kq[u] = vcd[e];
+        if (images) {  // the same image, counted from the nearest one now
+          const ImageOffset o = offset_at_build(st_built, ref, N, i, jq[u], vcd[e]);
+          int n0, n1, n2;
+          min_image(st, pos[jq[u]] - xi, pos[N + jq[u]] - yi, pos[2 * N + jq[u]] - zi, n0, n1, n2);
+          kq[u] = make_code(o.n[0] - n0, o.n[1] - n1, o.n[2] - n2);
+        }
       }
     }
   };
@@ -1389,15 +1420,15 @@ void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs,
 bool rev_in_candidates(int64_t N, bool batch) { return !batch && N < kFewAtoms; }
 
 template <int G>
-static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V, const Lists& L,
-                            float4* disp, hipStream_t s) {
+static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const double* ref,
+                            const StructInfo* st_ref, const Lists& V, const Lists& L, float4* disp, hipStream_t s) {
   const dim3 grid = grid_for(b.N * G);
   if (batch)
     hipLaunchKernelGGL((k_filter_rows<true, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
-                       st0, V, b.rcR2, b.rcA2, L, b.overflow);
+                       st0, ref, st_ref, V, b.rcR2, b.rcA2, L, b.overflow);
   else
     hipLaunchKernelGGL((k_filter_rows<false, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
-                       st0, V, b.rcR2, b.rcA2, L, b.overflow);
+                       st0, ref, st_ref, V, b.rcR2, b.rcA2, L, b.overflow);
   if (batch)
     hipLaunchKernelGGL((k_reverse_from_candidates<true, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        b.pos, b.types, b.sid, b.structs, disp, b.overflow + 2);
@@ -1407,10 +1438,10 @@ static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batc
                        (const StructInfo*)nullptr, (float4*)nullptr, b.overflow + 2);
 }
 
-void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                        const Lists& L, float4* disp, hipStream_t s) {
-  if (b.N < kFewAtoms) launch_filter_g<16>(b, st0, batch, V, L, disp, s);
-  else launch_filter_g<4>(b, st0, batch, V, L, disp, s);
+void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const double* ref,
+                        const StructInfo* st_ref, const Lists& V, const Lists& L, float4* disp, hipStream_t s) {
+  if (b.N < kFewAtoms) launch_filter_g<16>(b, st0, batch, ref, st_ref, V, L, disp, s);
+  else launch_filter_g<4>(b, st0, batch, ref, st_ref, V, L, disp, s);
 }
 
 // flag = any atom whose displacement since the last build, plus horizon

@@ -108,15 +108,19 @@ void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs,
                        bool batch, const Lists& L, const Lists* V, int32_t* bad, hipStream_t s);
 void launch_build_verlet(const BuildArgs& b, const Lists& V, hipStream_t s);
 // After a gated re-sort: pos/vel/types/ext <- their permuted copies, pos_ref <- pos
-// (and *count += 1 when count is given).
+// (*count += 1 when count is given, *st_ref = *st when st_ref is).
 void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, const int32_t* types2,
                            const int32_t* ext2, double* pos, double* vel, int32_t* types, int32_t* ext,
                            double* pos_ref, const int32_t* gate, hipStream_t s,
-                           double* mu_cum = nullptr, int32_t* count = nullptr);
+                           double* mu_cum = nullptr, int32_t* count = nullptr,
+                           const StructInfo* st = nullptr, StructInfo* st_ref = nullptr);
 // Whether launch_filter_rows leaves the candidates' reverse positions in L.revR.
 bool rev_in_candidates(int64_t N, bool batch);
-void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const Lists& V,
-                        const Lists& L, float4* disp, hipStream_t s);
+// Exact rows L and the candidates' map from the candidate rows V.  ref: the
+// positions that V was built at; st_ref: the structure then (device; batch only,
+// else the structure is st0 throughout).
+void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const double* ref,
+                        const StructInfo* st_ref, const Lists& V, const Lists& L, float4* disp, hipStream_t s);
 // flag = 1 if an atom moved more than allowed since the last build, or will
 // have once it moves `horizon` times its current speed further (vel given);
 // with mu_cum (box scaling since the build, NPT) the allowance shrinks to

@@ -88,3 +88,48 @@ def test_elastic_constants_of_a_small_cell(kind, a):
     print(f"[offsets] elastic {kind}: {got} (oracle {ref})", flush=True)
     np.testing.assert_allclose(got, ref, rtol=2e-3, atol=0.05)
     handle.close()
+
+
+@pytest.mark.parametrize("kind,a,n", [("fcc", 4.05, 2), ("diamond", 5.43, 2), ("primitive", 4.05, 4)])
+def test_images_stay_the_same_while_atoms_cross_half_the_cell(kind, a, n):
+    """Thermal motion takes the atoms that start half a cell vector apart across it and
+    back between two builds of the candidate rows, and the rows filtered from
+    them keep every image: the positions after 60 fs are those of rows built at
+    every step.  The atoms move at most 0.6 A; forces within 1e-4 eV/A of each other at
+    the same positions, mass 27, so 60 steps of 1 fs give differences of
+    1e-4 x 9.65e-3 / 27 x 60^2 / 2 < 7e-5 A, doubled for their growth."""
+    h = synth.hparams(1, 6.0, 5.0, 4, 4, 5, 5, 4, 2, 0, 16, 0)
+    p = synth.solid_params(h, O.num_descriptors(h), O.num_params(h), seed=3)
+    if kind == "primitive":
+        pos, types, box = _cell("fcc-4", 0.0)
+        types[:] = 0
+    else:
+        pos, types, box = synth.lattice(kind, n, a, 0.0, 1)
+    vel = synth.maxwell_velocities(np.array([26.98])[types], 300.0)
+    want = None
+    for skin in (0.0, 0.3, 1.0):
+        handle = nep.Handle(h, p, skin=skin)
+        got = handle.md_run(pos, vel, types, [26.98], box, 1.0, 60, 10)[0]
+        want = got if want is None else want
+        print(f"[offsets] {kind} skin {skin}: moved {np.abs(got - pos).max():.2f}, differs {np.abs(got - want).max():.1e}",
+              flush=True)
+        assert np.abs(got - want).max() < 1.4e-4
+        handle.close()
+
+
+def test_images_stay_the_same_under_a_barostat():
+    """The same with a cell that changes: a run whose skin is rebuilt now and then against
+    one with so small a skin that every step rebuilds."""
+    h = synth.hparams(1, 6.0, 5.0, 4, 4, 5, 5, 4, 2, 0, 16, 0)
+    p = synth.solid_params(h, O.num_descriptors(h), O.num_params(h), seed=3)
+    pos, types, box = synth.lattice("fcc", 2, 4.05, 0.0, 1)
+    vel = synth.maxwell_velocities(np.array([26.98])[types], 300.0)
+    ens = dict(kind="npt_berendsen", temperature=300.0, tau_t=100.0, pressure=2.0, tau_p=500.0, compressibility=0.01)
+    out = []
+    for skin in (1e-6, 0.8):
+        handle = nep.Handle(h, p, skin=skin)
+        out.append(handle.md_run_ensemble(pos, vel, types, [26.98], box, 1.0, 40, 10, ens))
+        handle.close()
+    err = np.abs(out[0][0] - out[1][0]).max()
+    print(f"[offsets] barostat: cell {box[0]:.4f} -> {out[0][2][0]:.4f}, positions differ by {err:.1e}", flush=True)
+    assert abs(out[0][2][0] - box[0]) > 1e-5 and err < 1.4e-4
