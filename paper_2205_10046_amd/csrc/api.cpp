@@ -384,7 +384,7 @@ struct nep_handle {
   double *partial = nullptr, *totals = nullptr, *thermo = nullptr, *mass = nullptr, *inv_mass = nullptr;
   int64_t thermo_cap = 0;
   int32_t *types_ext = nullptr, *types = nullptr, *types2 = nullptr, *sid_ext = nullptr, *sid = nullptr;
-  int32_t *key = nullptr, *perm = nullptr, *ext_id = nullptr, *ext_id2 = nullptr, *inv = nullptr;
+  int32_t *key = nullptr, *cell = nullptr, *perm = nullptr, *ext_id = nullptr, *ext_id2 = nullptr, *inv = nullptr;
   int32_t *cell_count = nullptr, *cell_fill = nullptr, *cell_start = nullptr;
   int32_t *rows = nullptr, *tblk = nullptr, *tex = nullptr, *flags = nullptr;
   StructInfo* structs = nullptr;
@@ -495,7 +495,7 @@ struct nep_handle {
     dev_free(vel_ext); dev_free(out_e); dev_free(out_f); dev_free(out_w);
     dev_free(partial); dev_free(totals); dev_free(thermo); dev_free(mass); dev_free(inv_mass);
     dev_free(types_ext); dev_free(types); dev_free(types2); dev_free(sid_ext); dev_free(sid);
-    dev_free(key); dev_free(perm); dev_free(ext_id); dev_free(ext_id2); dev_free(inv);
+    dev_free(key); dev_free(cell); dev_free(perm); dev_free(ext_id); dev_free(ext_id2); dev_free(inv);
     dev_free(cell_count); dev_free(cell_fill); dev_free(cell_start);
     dev_free(rows); dev_free(tblk); dev_free(tex); dev_free(flags);
     dev_free(structs); dev_free(offs);
@@ -780,7 +780,7 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     const int64_t c = N;
     dev_alloc(h->pos_ext, 3 * c); dev_alloc(h->pos, 3 * c);
     dev_alloc(h->types_ext, c); dev_alloc(h->types, c); dev_alloc(h->sid_ext, c); dev_alloc(h->sid, c);
-    dev_alloc(h->key, c); dev_alloc(h->perm, c); dev_alloc(h->inv, c);
+    dev_alloc(h->key, c); dev_alloc(h->cell, c); dev_alloc(h->perm, c); dev_alloc(h->inv, c);
     dev_alloc(h->out_e, c); dev_alloc(h->out_f, 3 * c); dev_alloc(h->out_w, 9 * c);
     dev_alloc(h->q, (size_t)c * M.NDp); dev_alloc(h->fp, (size_t)c * M.NDp);
     dev_alloc(h->U, c); dev_alloc(h->sums, (size_t)sums_floats(M) * c);
@@ -830,6 +830,7 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.sid_ext = h->sid_ext;
   b.structs = h->structs;
   b.key = h->key;
+  b.cell = h->cell;
   b.cell_count = h->cell_count;
   b.cell_fill = h->cell_fill;
   b.cell_start = h->cell_start;

@@ -91,7 +91,7 @@ __global__ void k_cell_key(BuildArgs b) {
   if (e >= b.N || gated_off(b.gate)) return;
   const StructInfo& st = b.structs[struct_of(b, e)];
   if (st.mode != kModeCells) {  // one cell, in caller order (k_cell_scatter)
-    b.key[e] = st.cell_off;
+    b.key[e] = ~st.cell_off;
     if (e == st.start) b.cell_count[st.cell_off] = (int32_t)st.count;
     return;
   }
@@ -133,10 +133,9 @@ __global__ void __launch_bounds__(1024) k_scan_1block(const int32_t* __restrict_
 __global__ void k_cell_scatter(BuildArgs b) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= b.N || gated_off(b.gate)) return;
-  const StructInfo& st = b.structs[struct_of(b, e)];
-  int k = b.key[e];
-  if (st.mode != kModeCells) {
-    b.perm[b.cell_start[k] + (e - st.start)] = (int32_t)e;
+  const int k = b.key[e];
+  if (k < 0) {
+    b.perm[b.cell_start[~k] + (e - b.structs[struct_of(b, e)].start)] = (int32_t)e;
     return;
   }
   int slot = atomicAdd(&b.cell_fill[k], 1);
@@ -219,6 +218,7 @@ __global__ void k_gather_atoms(BuildArgs b) {
   b.pos[2 * N + k] = z;
   b.types[k] = t;
   b.sid[k] = struct_of(b, e);
+  b.cell[k] = b.key[e];
   if (b.vel_src)
     for (int c = 0; c < 3; ++c) b.vel_dst[c * N + k] = b.vel_src[c * N + e];
   if (b.ext_in) b.ext_out[k] = b.ext_in[e];
@@ -333,8 +333,8 @@ struct RowSink {
   }
 };
 
-// Rows of the atoms of cell-mode structures.  A block takes the atoms of one
-// cell, G lanes each.  The atoms of the (up to 27) stencil cells are
+// Rows of the atoms of cell-mode structures.  A block takes a part of a cell's
+// atoms, G lanes each.  The atoms of the (up to 27) stencil cells are
 // staged in LDS once, as float32 positions relative to one atom of the cell,
 // in increasing internal index; every lane group walks them G at a
 // time and lists those within the cutoff plus a bound of the float32 error,
@@ -345,65 +345,63 @@ struct RowSink {
 // arithmetic, then the walk.  A walk of each atom over its stencil, four
 // lanes to it, was 510 dependent position loads and float64 tests per atom of
 // the 4-species alloy: 179 us for 131,072 atoms and 58 us more to part the
-// rows by cutoff, 87 us for 3,995.  This takes 136 and 14 us, parting included.
+// rows by cutoff, 87 us for 3,995.  This takes 130 and 14 us, parting included.
 // Members staged in LDS and stored along consecutive atoms: 132 (and 75 for
 // 66 us where the rows take a skin); one wave per cell: 158 to 162.
 constexpr int kCellStage = 1024;  // staged candidates
 constexpr int kCellList = 128;    // listed candidates of an atom between two exact passes
+constexpr int kCellRun = 64;      // consecutive cells of an XCD
 
-template <bool EXACT, int G>
-__global__ void __launch_bounds__(kBlock) k_build_rows_cells(
-    const double* __restrict__ pos, int64_t N, const StructInfo* __restrict__ structs, int32_t n_struct,
-    const int32_t* __restrict__ cell_start, const int32_t* __restrict__ cell_count, int32_t n_cells, double rcR2,
-    double rcA2, Lists V, Lists L, int32_t* __restrict__ overflow, const int32_t* gate) {
-  constexpr int kCellAtoms = kBlock / G;  // atoms of a block at a time
-  __shared__ float4 stage[kCellStage];
-  __shared__ int32_t list[kCellAtoms][kCellList];
-  __shared__ int32_t c_start[27], c_first[28];
-  __shared__ float reach2[kBlock / 64];
-  if (gated_off(gate)) return;
-  const int cell = (int)xcd_block();
-  const int count = cell_count[cell], begin = cell_start[cell];
-  if ((int)blockIdx.y * kCellAtoms >= count) return;
-  // the structure this cell belongs to
-  int lo = 0, hi = n_struct - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (structs[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+template <int G>
+struct CellPart {  // LDS of a block of the row builder
+  static constexpr int kAtoms = kBlock / G;  // atoms of a part of a cell
+  float4 stage[kCellStage];
+  int32_t list[kAtoms][kCellList];
+  int32_t start[27], first[28];  // of the stencil's cells: first atom, running count of candidates
+  float reach2[kBlock / 64];
+};
+
+// Starts and running counts of the cells around `cell` in increasing order, by a whole block.
+template <int G>
+__device__ __forceinline__ void cell_stencil(CellPart<G>& s, const StructInfo& st, int cell,
+                                             const int32_t* __restrict__ cell_start,
+                                             const int32_t* __restrict__ cell_count) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int c = cell - st.cell_off, cx = c % st.ncell[0], cy = c / st.ncell[0] % st.ncell[1],
+            cz = c / (st.ncell[0] * st.ncell[1]);
+  int sx[3], sy[3], sz[3];
+  const int nx = stencil_1d(cx, st.ncell[0], st.pbc[0], sx), ny = stencil_1d(cy, st.ncell[1], st.pbc[1], sy),
+            nz = stencil_1d(cz, st.ncell[2], st.pbc[2], sz);
+  if (tid < 64) {
+    int32_t n = 0;
+    if (tid < nx * ny * nz) {
+      const int x = tid % nx, y = tid / nx % ny, z = tid / (nx * ny);
+      const int px = x == 0 ? sx[0] : (x == 1 ? sx[1] : sx[2]), py = y == 0 ? sy[0] : (y == 1 ? sy[1] : sy[2]),
+                pz = z == 0 ? sz[0] : (z == 1 ? sz[1] : sz[2]);
+      const int k = st.cell_off + (pz * st.ncell[1] + py) * st.ncell[0] + px;
+      s.start[tid] = cell_start[k];
+      n = cell_count[k];
+    }
+    int32_t run = n;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+      const int32_t v = __shfl_up(run, off);
+      if (lane >= off) run += v;
+    }
+    if (tid < 27) s.first[tid + 1] = run;
+    if (tid == 0) s.first[0] = 0;
   }
-  const StructInfo& st = structs[lo];
-  if (st.mode != kModeCells) return;
+}
+
+// The rows of the atoms [a0, a0 + kBlock / G) of a cell of `count` atoms from `begin` on, by a whole block.
+template <bool EXACT, int G>
+__device__ __forceinline__ void cell_part_rows(CellPart<G>& s, const StructInfo& st, int begin, int count, int a0,
+                                               const double* __restrict__ pos, int64_t N, double rcR2, double rcA2,
+                                               const Lists& V, const Lists& L, int32_t* __restrict__ overflow) {
   const int tid = threadIdx.x, sub = tid & (G - 1), lane = tid & 63;
   const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << (lane & ~(G - 1));
-  // the stencil: starts and running counts of its cells in increasing order
-  {
-    const int c = cell - st.cell_off, cx = c % st.ncell[0], cy = c / st.ncell[0] % st.ncell[1],
-              cz = c / (st.ncell[0] * st.ncell[1]);
-    int sx[3], sy[3], sz[3];
-    const int nx = stencil_1d(cx, st.ncell[0], st.pbc[0], sx), ny = stencil_1d(cy, st.ncell[1], st.pbc[1], sy),
-              nz = stencil_1d(cz, st.ncell[2], st.pbc[2], sz);
-    if (tid < 64) {
-      int32_t n = 0;
-      if (tid < nx * ny * nz) {
-        const int x = tid % nx, y = tid / nx % ny, z = tid / (nx * ny);
-        const int px = x == 0 ? sx[0] : (x == 1 ? sx[1] : sx[2]), py = y == 0 ? sy[0] : (y == 1 ? sy[1] : sy[2]),
-                  pz = z == 0 ? sz[0] : (z == 1 ? sz[1] : sz[2]);
-        const int k = st.cell_off + (pz * st.ncell[1] + py) * st.ncell[0] + px;
-        c_start[tid] = cell_start[k];
-        n = cell_count[k];
-      }
-      int32_t run = n;
-#pragma unroll
-      for (int off = 1; off < 32; off <<= 1) {
-        const int32_t v = __shfl_up(run, off);
-        if (lane >= off) run += v;
-      }
-      if (tid < 27) c_first[tid + 1] = run;
-      if (tid == 0) c_first[0] = 0;
-    }
-  }
-  __syncthreads();
-  const int total = c_first[27];
+  const float rc2 = (float)rcR2;
+  const int total = s.first[27];
   const bool any_wrap = st.pbc[0] || st.pbc[1] || st.pbc[2];
   // float32 position relative to the cell's first atom (the nearest image of it)
   const double rx = pos[begin], ry = pos[N + begin], rz = pos[2 * N + begin];
@@ -423,98 +421,154 @@ __global__ void __launch_bounds__(kBlock) k_build_rows_cells(
   // at most half the box; with fewer than four cells every staged candidate is listed.
   bool near_all = false;
   for (int k = 0; k < 3; ++k) near_all = near_all || (st.pbc[k] && st.ncell[k] < 4);
-  const float rc2 = (float)rcR2;
-
-  for (int a0 = blockIdx.y * kCellAtoms; a0 < count; a0 += gridDim.y * kCellAtoms) {
-    const int a = a0 + tid / G;
-    const bool live = a < count;
-    const int64_t i = begin + min(a, count - 1);
-    float xi, yi, zi;
-    relative(i, xi, yi, zi);
-    const double pxi = pos[i], pyi = pos[N + i], pzi = pos[2 * N + i];
-    RowSink<EXACT> sink{V, L, N, i, false};
-    int32_t* mine = list[tid / G];
-    int listed = 0;
-    // the float64 test of the listed candidates, sixteen at a time
-    auto exact_pass = [&]() __attribute__((always_inline)) {
-      for (int q0 = 0; q0 < listed; q0 += G) {
-        const int q = q0 + sub;
-        bool ta = false, to = false;
-        int32_t j = 0;
-        if (q < listed) {
-          j = mine[q];
-          double Dx, Dy, Dz;
-          {
+  const int a = a0 + tid / G;
+  const bool live = a < count;
+  const int64_t i = begin + min(a, count - 1);
+  float xi, yi, zi;
+  relative(i, xi, yi, zi);
+  const double pxi = pos[i], pyi = pos[N + i], pzi = pos[2 * N + i];
+  RowSink<EXACT> sink{V, L, N, i, false};
+  int32_t* mine = s.list[tid / G];
+  int listed = 0;
+  // the float64 test of the listed candidates, G at a time
+  auto exact_pass = [&]() __attribute__((always_inline)) {
+    for (int q0 = 0; q0 < listed; q0 += G) {
+      const int q = q0 + sub;
+      bool ta = false, to = false;
+      int32_t j = 0;
+      if (q < listed) {
+        j = mine[q];
+        double Dx, Dy, Dz;
+        {
 #pragma clang fp contract(off)
-            Dx = pos[j] - pxi;
-            Dy = pos[N + j] - pyi;
-            Dz = pos[2 * N + j] - pzi;
-          }
-          int n0, n1, n2;
-          min_image(st, Dx, Dy, Dz, n0, n1, n2);
-          if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
-            double dx, dy, dz;
-            image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
-            const double r2 = norm2_exact(dx, dy, dz);
-            ta = EXACT && r2 < rcA2;
-            to = !ta && r2 < rcR2;
-          }
+          Dx = pos[j] - pxi;
+          Dy = pos[N + j] - pyi;
+          Dz = pos[2 * N + j] - pzi;
         }
-        const uint64_t ma = __ballot(ta) & gmask, mo = __ballot(to) & gmask;
-        if (ta) sink.put(true, sink.na + lanes_below(ma), j, kCodeCenter);
-        if (to) sink.put(false, sink.no + lanes_below(mo), j, kCodeCenter);
-        sink.na += __popcll(ma);
-        sink.no += __popcll(mo);
-      }
-      listed = 0;
-    };
-    for (int base = 0; base < total; base += kCellStage) {
-      const int n = min(kCellStage, total - base);
-      __syncthreads();  // the previous stage has been walked
-      float far2 = 0.f;
-      for (int k = tid; k < n; k += kBlock) {
-        int l = 0, h = 26;  // last stencil cell whose first candidate is at or before base + k
-        while (l < h) {
-          const int mid = (l + h + 1) >> 1;
-          if (c_first[mid] <= base + k) l = mid; else h = mid - 1;
-        }
-        const int32_t j = c_start[l] + base + k - c_first[l];
-        float x, y, z;
-        relative(j, x, y, z);
-        far2 = fmaxf(far2, x * x + y * y + z * z);
-        stage[k] = make_float4(x, y, z, __int_as_float(j));
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) far2 = fmaxf(far2, __shfl_xor(far2, off));
-      if (lane == 0) reach2[tid >> 6] = far2;
-      __syncthreads();
-      // the squared float32 distance of a pair is off by less than 1e-6 (r_c^2 + 4 of
-      // the largest squared coordinate): two positions rounded to 2^-24, their
-      // difference, and three products
-      float m2 = reach2[0];
-#pragma unroll
-      for (int w = 1; w < kBlock / 64; ++w) m2 = fmaxf(m2, reach2[w]);
-      const float thr = near_all ? INFINITY : rc2 + 1e-6f * (rc2 + 8.f * (m2 + xi * xi + yi * yi + zi * zi));
-      for (int k0 = 0; k0 < n; k0 += G) {
-        const int k = k0 + sub;
-        const float4 c = stage[min(k, n - 1)];
-        const float dx = c.x - xi, dy = c.y - yi, dz = c.z - zi;
-        // (written so that a non-finite distance lists the candidate)
-        const bool near = live && k < n && !(dx * dx + dy * dy + dz * dz > thr);
-        const uint64_t m = __ballot(near) & gmask;
-        if (near) mine[listed + lanes_below(m)] = __float_as_int(c.w);
-        listed += __popcll(m);
-        if (listed > kCellList - G) {  // the same for the lanes of an atom
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          exact_pass();
-          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        int n0, n1, n2;
+        min_image(st, Dx, Dy, Dz, n0, n1, n2);
+        if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
+          double dx, dy, dz;
+          image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
+          const double r2 = norm2_exact(dx, dy, dz);
+          ta = EXACT && r2 < rcA2;
+          to = !ta && r2 < rcR2;
         }
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      exact_pass();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const uint64_t ma = __ballot(ta) & gmask, mo = __ballot(to) & gmask;
+      if (ta) sink.put(true, sink.na + lanes_below(ma), j, kCodeCenter);
+      if (to) sink.put(false, sink.no + lanes_below(mo), j, kCodeCenter);
+      sink.na += __popcll(ma);
+      sink.no += __popcll(mo);
     }
-    if (live) sink.template finish<G>(sub, overflow);
+    listed = 0;
+  };
+  for (int base = 0; base < total; base += kCellStage) {
+    const int n = min(kCellStage, total - base);
+    __syncthreads();  // the previous stage has been walked
+    float far2 = 0.f;
+    for (int k = tid; k < n; k += kBlock) {
+      int l = 0, h = 26;  // last stencil cell whose first candidate is at or before base + k
+      while (l < h) {
+        const int mid = (l + h + 1) >> 1;
+        if (s.first[mid] <= base + k) l = mid; else h = mid - 1;
+      }
+      const int32_t j = s.start[l] + base + k - s.first[l];
+      float x, y, z;
+      relative(j, x, y, z);
+      far2 = fmaxf(far2, x * x + y * y + z * z);
+      s.stage[k] = make_float4(x, y, z, __int_as_float(j));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) far2 = fmaxf(far2, __shfl_xor(far2, off));
+    if (lane == 0) s.reach2[tid >> 6] = far2;
+    __syncthreads();
+    // the squared float32 distance of a pair is off by less than 1e-6 (r_c^2 + 4 of
+    // the largest squared coordinate): two positions rounded to 2^-24, their
+    // difference, and three products
+    float m2 = s.reach2[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / 64; ++w) m2 = fmaxf(m2, s.reach2[w]);
+    const float thr = near_all ? INFINITY : rc2 + 1e-6f * (rc2 + 8.f * (m2 + xi * xi + yi * yi + zi * zi));
+    for (int k0 = 0; k0 < n; k0 += G) {
+      const int k = k0 + sub;
+      const float4 c = s.stage[min(k, n - 1)];
+      const float dx = c.x - xi, dy = c.y - yi, dz = c.z - zi;
+      // (written so that a non-finite distance lists the candidate)
+      const bool near = live && k < n && !(dx * dx + dy * dy + dz * dz > thr);
+      const uint64_t m = __ballot(near) & gmask;
+      if (near) mine[listed + lanes_below(m)] = __float_as_int(c.w);
+      listed += __popcll(m);
+      if (listed > kCellList - G) {  // the same for the lanes of an atom
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        exact_pass();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    exact_pass();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  if (live) sink.template finish<G>(sub, overflow);
+}
+
+// The parts of a block's cell, the blocks along y sharing a cell.
+template <bool EXACT, int G>
+__global__ void __launch_bounds__(kBlock) k_build_rows_cells(
+    const double* __restrict__ pos, int64_t N, const StructInfo* __restrict__ structs, int32_t n_struct,
+    const int32_t* __restrict__ cell_start, const int32_t* __restrict__ cell_count, double rcR2, double rcA2, Lists V,
+    Lists L, int32_t* __restrict__ overflow, const int32_t* gate) {
+  __shared__ CellPart<G> s;
+  if (gated_off(gate)) return;
+  const int cell = (int)xcd_runs<kCellRun>();
+  const int count = cell_count[cell], begin = cell_start[cell];
+  if ((int)blockIdx.y * s.kAtoms >= count) return;
+  // the structure this cell belongs to
+  int lo = 0, hi = n_struct - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (structs[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+  }
+  const StructInfo& st = structs[lo];
+  if (st.mode != kModeCells) return;
+  cell_stencil(s, st, cell, cell_start, cell_count);
+  __syncthreads();
+  for (int a0 = blockIdx.y * s.kAtoms; a0 < count; a0 += gridDim.y * s.kAtoms)
+    cell_part_rows<EXACT, G>(s, st, begin, count, a0, pos, N, rcR2, rcA2, V, L, overflow);
+}
+
+// The parts whose first atom lies in a block's range of half a part's atoms: mostly one or none in
+// crowded cells, one for each cell where they hold an atom or two.
+template <int G>
+constexpr int cell_range() { return kBlock / G / 2; }
+
+template <bool EXACT, int G>
+__global__ void __launch_bounds__(kBlock) k_build_rows_ranges(
+    const double* __restrict__ pos, int64_t N, const int32_t* __restrict__ sid, const StructInfo* __restrict__ structs,
+    const int32_t* __restrict__ cell_id, const int32_t* __restrict__ cell_start, const int32_t* __restrict__ cell_count,
+    double rcR2, double rcA2, Lists V, Lists L, int32_t* __restrict__ overflow, const int32_t* gate) {
+  __shared__ CellPart<G> s;
+  if (gated_off(gate)) return;
+  constexpr int R = cell_range<G>();
+  const int lane = threadIdx.x & 63;
+  for (int64_t range = xcd_block() * R; range < N; range += (int64_t)gridDim.x * R) {
+    int32_t my_cell = -1;
+    bool head = false;
+    if (lane < R && range + lane < N) {
+      my_cell = cell_id[range + lane];
+      if (my_cell >= 0) head = (range + lane - cell_start[my_cell]) % s.kAtoms == 0;
+    }
+    for (uint64_t heads = __ballot(head); heads; heads &= heads - 1) {  // the same in every wave
+      const int at = __builtin_ctzll(heads);
+      const int cell = __builtin_amdgcn_readfirstlane(__shfl(my_cell, at));
+      const StructInfo& st = structs[sid[range + at]];
+      const int begin = cell_start[cell];
+      __syncthreads();  // the part before has been walked
+      cell_stencil(s, st, cell, cell_start, cell_count);
+      __syncthreads();
+      cell_part_rows<EXACT, G>(s, st, begin, cell_count[cell], (int)(range + at - begin), pos, N, rcR2, rcA2, V, L,
+                               overflow);
+    }
   }
 }
 
@@ -953,15 +1007,32 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
 // 32,000.
 constexpr int64_t kFewAtoms = 16384;
 
-// blocks along y share a cell's atoms: enough for cells of half as many again
-// as the average (fuller ones take another turn)
+// A grid stays below 2^32 threads.
+constexpr int64_t kMaxBlocks = 1 << 22;
+
+// Blocks to cells, in runs of cells to an XCD (with an eighth of the grid to each,
+// a slab of 64,000 atoms in four times its volume left most of them idle: 576 us
+// for the evaluation, 418 now).  Blocks to ranges of atoms where the cells hold
+// fewer than two on average: most are empty then, and the others crowded where
+// a box that is mostly empty has larger cells (5,562 atoms in a thousand times
+// their volume: 6,970 us for the evaluation with blocks to cells, 430 with
+// ranges; 64,000 in twenty times: 909 and 615).  In full cells the ranges are the
+// slower: 186 us against 130 for 131,072 atoms, 14 registers more for the loop
+// over parts and two parts to some blocks.
 template <bool EXACT, int G>
 static void launch_cells(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s) {
+  if (b.N < 2 * (int64_t)b.n_cells || b.n_cells > kMaxBlocks) {
+    const int64_t blocks = std::min<int64_t>(div_up(b.N, cell_range<G>()), kMaxBlocks);
+    hipLaunchKernelGGL((k_build_rows_ranges<EXACT, G>), dim3((unsigned)blocks), dim3(kBlock), 0, s, b.pos, b.N, b.sid,
+                       b.structs, b.cell, b.cell_start, b.cell_count, b.rcR2, b.rcA2, V, L, b.overflow, b.gate);
+    return;
+  }
+  // blocks along y share a cell's atoms: enough for cells of half as many again
+  // as the average (fuller ones take another turn)
   const int64_t per = b.N * 3 / (2 * (int64_t)b.n_cells) + 1;
   const int64_t y = std::min<int64_t>(div_up(per, kBlock / G), 64);
   hipLaunchKernelGGL((k_build_rows_cells<EXACT, G>), dim3((unsigned)b.n_cells, (unsigned)y), dim3(kBlock), 0, s, b.pos,
-                     b.N, b.structs, b.n_struct, b.cell_start, b.cell_count, b.n_cells, b.rcR2, b.rcA2, V, L,
-                     b.overflow, b.gate);
+                     b.N, b.structs, b.n_struct, b.cell_start, b.cell_count, b.rcR2, b.rcA2, V, L, b.overflow, b.gate);
 }
 
 template <bool EXACT>
@@ -1548,6 +1619,7 @@ __global__ void __launch_bounds__(kOneThreads) k_order_one_block(BuildArgs b) {
     key[q] = ~st.cell_off;
     if (st.mode == kModeCells) key[q] = cell_of(st, x[q], y[q], z[q]);
     if (e >= N) continue;
+    b.key[e] = key[q];
     if (key[q] >= 0) atomicAdd(&cell[key[q]], 1);
     else if (e == st.start) cell[st.cell_off] = (int32_t)st.count;
   }

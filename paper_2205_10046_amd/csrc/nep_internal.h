@@ -201,4 +201,13 @@ __device__ __forceinline__ int64_t xcd_block() {
   return x * q + (x < r ? x : r) + k;
 }
 
+// The same in runs of RUN consecutive numbers to an XCD, for work that is
+// unevenly spread over the whole range (cells of a box with vacuum): no XCD gets
+// more of the full part than the others.  A bijection on [0, gridDim.x) too.
+template <int RUN>
+__device__ __forceinline__ int64_t xcd_runs() {
+  const int64_t b = blockIdx.x, x = b % kXcds, k = b / kXcds, turn = kXcds * RUN;
+  return b < gridDim.x / turn * turn ? k / RUN * turn + x * RUN + k % RUN : b;
+}
+
 }  // namespace nep

@@ -12,7 +12,8 @@ struct BuildArgs {
   const int32_t* sid_ext;     // structure of each source atom (not read when n_struct is 1)
   const int32_t* ext_src;     // caller index of each source atom (NULL: the source index)
   const StructInfo* structs;
-  int32_t* key;               // [N]
+  int32_t* key;               // [N] cell of each source atom; ~cell in a structure without cells
+  int32_t* cell;              // [N] the same of each internal atom
   int32_t* cell_count;        // [n_cells]
   int32_t* cell_fill;         // [n_cells]
   int32_t* cell_start;        // [n_cells]

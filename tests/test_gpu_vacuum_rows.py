@@ -1,0 +1,107 @@
+"""Structures in vacuum: clusters and slabs that leave most cells of their box
+empty and, where the box is so large that its cells are, crowd the others.
+Rows are whole numbers and equal the oracle's; copies of a cluster far apart
+in one box give the rows, and the energies, of the one."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2205_10046_amd import nep, synth
+
+pytestmark = pytest.mark.gpu
+
+H = synth.hparams(1, 4.6, 3.7, 2, 2, 2, 2, 2, 0, 0, 4, 1)
+
+
+def _cluster(n, seed=0):
+    """The n atoms of a noisy crystal next to the origin, in random order."""
+    pos, _, box = synth.lattice("fcc", int((n / 2) ** (1 / 3)) + 3, 4.05, 0.1, 1, seed)
+    pos = pos - pos.mean(1, keepdims=True)
+    keep = np.argsort((pos ** 2).sum(0))[:n]
+    return np.ascontiguousarray(pos[:, np.random.default_rng(seed).permutation(keep)])
+
+
+def _sorted(rows):
+    return [sorted(zip(j.tolist(), map(tuple, s.tolist()))) for j, s in rows]
+
+
+@pytest.mark.parametrize("n,side,pbc", [
+    (300, 60.0, (1, 1, 1)),       # cells of the cutoff, most of them empty
+    (300, 3000.0, (1, 0, 1)),     # the whole cluster in a few cells
+    (1700, 400.0, (1, 1, 1)),     # more cells than one block orders
+])
+def test_rows_of_a_cluster_equal_the_oracle(n, side, pbc):
+    pos = _cluster(n) + side / 2
+    near = pos - side / 2 + 40.0          # the oracle's box: as open, but small
+    handle = nep.Handle(H, synth.random_params(O.num_params(H), seed=1))
+    for which, rc in ((0, 4.6), (1, 3.7)):
+        got = handle.neighbors(pos, (side * np.eye(3)).reshape(9), which, pbc, cap=256)
+        print(f"[vacuum] {n} atoms in {side} A, row {which}", flush=True)
+        assert _sorted(got) == _sorted(O.pairs(near, (80.0 * np.eye(3)).reshape(9), rc, (0, 0, 0)))
+    handle.close()
+
+
+@pytest.mark.parametrize("n,copies,side", [(150, 12, 500.0), (150, 120, 500.0)])
+def test_copies_of_a_cluster_equal_the_one(n, copies, side):
+    one = _cluster(n)
+    p = synth.random_params(O.num_params(H), seed=1)
+    small = (80.0 * np.eye(3)).reshape(9)
+    ref = O.evaluate(H, p, one + 40.0, np.zeros(n, np.int32), small, (0, 0, 0))
+    rng = np.random.default_rng(3)
+    m = int(side // 90)                       # sites 90 A apart
+    site = rng.choice(m ** 3, copies, replace=False)
+    at = (np.stack(np.unravel_index(site, (m, m, m))) + 0.5) * 90.0
+    pos = np.concatenate([one + c[:, None] for c in at.T], 1)
+    mix = rng.permutation(pos.shape[1])
+    handle = nep.Handle(H, p)
+    got = handle.compute(pos[:, mix], np.zeros(len(mix), np.int32), (side * np.eye(3)).reshape(9))
+    back = np.argsort(mix)
+    U, F = got["U"][back].reshape(copies, n), got["F"][:, back].reshape(3, copies, n)
+    print(f"[vacuum] {copies} x {n}: |dU| {np.abs(U - ref['U']).max():.1e}", flush=True)
+    assert np.abs(U - ref["U"]).max() <= 1e-5 and np.abs(F - ref["F"][:, None]).max() <= 1e-4
+    handle.close()
+
+
+def test_a_batch_of_sparse_and_dense_cells():
+    """Structures with and without cells, full and empty ones, in one call."""
+    p = synth.random_params(O.num_params(H), seed=1)
+    dense, types, box = synth.lattice("fcc", 6, 4.05, 0.1, 1)
+    cells = [(_cluster(400) + 100.0, np.zeros(400, np.int32), (200.0 * np.eye(3)).reshape(9)),
+             (dense, types, box), (dense[:, :40] + 0.0, types[:40], (40.0 * np.eye(3)).reshape(9)),
+             (_cluster(700, 2) + 300.0, np.zeros(700, np.int32), (600.0 * np.eye(3)).reshape(9))]
+    import torch
+    for repeat in (1, 10):
+        pos, t, boxes, offs = synth.concat_structures(cells * repeat)
+        U = torch.empty(1, len(t), dtype=torch.float64, device="cuda")
+        handle = nep.Handle(H, p)
+        handle.compute_batch(offs, torch.tensor(pos, device="cuda"), torch.tensor(t, device="cuda"), boxes, None, U)
+        for k, c in enumerate(cells * repeat):
+            ref = O.evaluate(H, p, *c)["U"] if k < len(cells) else refs[k % len(cells)]
+            refs = [ref] if k == 0 else refs + [ref]
+            assert np.abs(U[0, offs[k]:offs[k + 1]].cpu().numpy() - ref).max() <= 1e-5
+        print(f"[vacuum] batch of {len(t)} atoms", flush=True)
+        handle.close()
+
+
+def test_more_cells_than_a_grid_of_blocks_could_take():
+    """4.3 million atoms in pairs, in a box of over 2^24 cells."""
+    import torch
+    m, a = 169, 7.0
+    n = 2 * 2150000
+    site = np.random.default_rng(4).choice(m ** 3, n // 2, replace=False)
+    at = np.stack(np.unravel_index(site, (m, m, m))) * a + 1.0
+    pos = np.empty((3, n))
+    pos[:, ::2], pos[:, 1::2] = at, at + np.array([[1.1], [0.7], [-0.4]])
+    assert np.floor(m * a / 4.6) ** 3 > 1 << 24 and 4 * n + 64 > 1 << 24
+    p = synth.random_params(O.num_params(H), seed=1)
+    box = (m * a * np.eye(3)).reshape(9)
+    out = [torch.empty(s, dtype=torch.float64, device="cuda") for s in ((n,), (3, n))]
+    handle = nep.Handle(H, p)
+    print(f"[vacuum] {n} atoms, {int(np.floor(m * a / 4.6)) ** 3} cells", flush=True)
+    handle.compute_dev(torch.tensor(pos, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda"), box, None,
+                       *out)
+    ref = O.evaluate(H, p, pos[:, :2] - pos[:, :1] + 20.0, np.zeros(2, np.int32), (40.0 * np.eye(3)).reshape(9),
+                     (0, 0, 0))
+    U, F = (x.cpu().numpy() for x in out)
+    assert np.abs(U.reshape(-1, 2) - ref["U"]).max() <= 1e-5 and np.abs(F.reshape(3, -1, 2) - ref["F"][:, None]).max() <= 1e-4
+    handle.close()
