@@ -205,6 +205,7 @@ struct Geometry {
   StructInfo st;
   int32_t n_cells;
   double volume;
+  bool coarse = false;  // cells larger than a cutoff asks for: one may hold every atom
 };
 
 // Cell inverse, face widths and the neighbour-search mode of one structure.
@@ -259,6 +260,7 @@ Geometry make_geometry(const double* box, const int32_t* pbc, int64_t n_atoms, d
     // a box that is mostly empty: larger cells, so that the passes over the cells do
     // not outweigh those over the atoms
     while (total > 4 * n_atoms + 64) {
+      g.coarse = true;
       int32_t& widest = *std::max_element(nc, nc + 3);
       total = total / widest * (widest / 2);
       widest /= 2;
@@ -818,6 +820,7 @@ struct Prepared {
   int32_t n_cells = 0;
   int64_t N = 0;
   bool batch = false;
+  bool coarse = false;           // some cells may be crowded (make_geometry)
 };
 
 BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, const int32_t* types_src,
@@ -842,6 +845,7 @@ BuildArgs build_args(nep_handle* h, const Prepared& pp, const double* pos_src, c
   b.rcA2 = h->hp.rc_angular * h->hp.rc_angular;
   b.overflow = h->flags;
   b.n_struct = (int32_t)pp.sts.size();
+  b.coarse = pp.coarse;
   b.n_types = h->M.T;
   b.per_type = h->hp.nn_per_type;
   for (const StructInfo& st : pp.sts) (st.mode == kModeCells ? b.cell_rows : b.wide_rows) = 1;
@@ -897,6 +901,7 @@ Prepared prepare_batch(nep_handle* h, int32_t S, const int64_t* offs, const doub
     cells += g.n_cells;
     max_density = std::max(max_density, (double)n / g.volume);
     pp.sts[k] = g.st;
+    pp.coarse = pp.coarse || g.coarse;
     if (k == 0) pp.geo = g;
   }
   pp.n_cells = cells;

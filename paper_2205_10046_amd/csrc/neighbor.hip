@@ -26,6 +26,14 @@
 
 namespace nep {
 
+// A grid stays below 2^32 threads.
+constexpr int64_t kMaxBlocks = 1 << 22;
+
+// Whether the row builder's blocks take ranges of atoms, see launch_cells.
+__host__ __device__ inline bool rows_by_ranges(const BuildArgs& b) {
+  return b.N < 2 * (int64_t)b.n_cells || b.n_cells > kMaxBlocks;
+}
+
 // Kernels of a rebuild take an optional gate: when it points to 0 they do
 // nothing, so an MD step can issue a fixed kernel sequence and let the device
 // decide whether the rows are rebuilt.
@@ -206,11 +214,43 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort(const int32_t* __restrict_
     if (lane + 64 * a < n) p[rank[a]] = v[a];
 }
 
-__global__ void k_gather_atoms(BuildArgs b) {
+// The same for cells that may hold any number of atoms, a thread to an atom: its
+// place is the number of smaller keys in its cell (in b.cell, which k_gather_atoms
+// takes the order from).  The whole cell by one lane, as above, would take n^2 / 4
+// dependent steps for n atoms; here n / 8 for each of them at once.
+__global__ void __launch_bounds__(kBlock) k_cell_rank(BuildArgs b) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= b.N || gated_off(b.gate)) return;
+  const int32_t e = b.perm[k], c = b.key[e];
+  if (c < 0) {  // a structure without cells: in order
+    b.cell[k] = e;
+    return;
+  }
+  const int32_t mine = b.ext_src ? b.ext_src[e] : e;
+  const int32_t* p = b.perm + b.cell_start[c];
+  const int n = b.cell_count[c];
+  int rank = 0;
+  for (int q = 0; q < n; q += 8) {
+    int32_t other[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) other[u] = p[min(q + u, n - 1)];
+    if (b.ext_src) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) other[u] = b.ext_src[other[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rank += q + u < n && other[u] < mine ? 1 : 0;
+  }
+  b.cell[b.cell_start[c] + rank] = e;
+}
+
+// `ranked`: the order is in b.cell (k_cell_rank), else in b.perm.
+__global__ void k_gather_atoms(BuildArgs b, bool ranked) {
   const int64_t N = b.N;
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= N || gated_off(b.gate)) return;
-  const int64_t e = b.perm[k];
+  const int64_t e = ranked ? b.cell[k] : b.perm[k];
+  if (ranked) b.perm[k] = (int32_t)e;
   const double x = b.pos_ext[e], y = b.pos_ext[N + e], z = b.pos_ext[2 * N + e];
   const int32_t t = b.types_ext[e];
   b.pos[k] = x;
@@ -218,7 +258,7 @@ __global__ void k_gather_atoms(BuildArgs b) {
   b.pos[2 * N + k] = z;
   b.types[k] = t;
   b.sid[k] = struct_of(b, e);
-  b.cell[k] = b.key[e];
+  if (rows_by_ranges(b)) b.cell[k] = b.key[e];
   if (b.vel_src)
     for (int c = 0; c < 3; ++c) b.vel_dst[c * N + k] = b.vel_src[c * N + e];
   if (b.ext_in) b.ext_out[k] = b.ext_in[e];
@@ -1007,9 +1047,6 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
 // 32,000.
 constexpr int64_t kFewAtoms = 16384;
 
-// A grid stays below 2^32 threads.
-constexpr int64_t kMaxBlocks = 1 << 22;
-
 // Blocks to cells, in runs of cells to an XCD (with an eighth of the grid to each,
 // a slab of 64,000 atoms in four times its volume left most of them idle: 576 us
 // for the evaluation, 418 now).  Blocks to ranges of atoms where the cells hold
@@ -1021,7 +1058,7 @@ constexpr int64_t kMaxBlocks = 1 << 22;
 // over parts and two parts to some blocks.
 template <bool EXACT, int G>
 static void launch_cells(const BuildArgs& b, const Lists& V, const Lists& L, hipStream_t s) {
-  if (b.N < 2 * (int64_t)b.n_cells || b.n_cells > kMaxBlocks) {
+  if (rows_by_ranges(b)) {
     const int64_t blocks = std::min<int64_t>(div_up(b.N, cell_range<G>()), kMaxBlocks);
     hipLaunchKernelGGL((k_build_rows_ranges<EXACT, G>), dim3((unsigned)blocks), dim3(kBlock), 0, s, b.pos, b.N, b.sid,
                        b.structs, b.cell, b.cell_start, b.cell_count, b.rcR2, b.rcA2, V, L, b.overflow, b.gate);
@@ -1619,7 +1656,7 @@ __global__ void __launch_bounds__(kOneThreads) k_order_one_block(BuildArgs b) {
     key[q] = ~st.cell_off;
     if (st.mode == kModeCells) key[q] = cell_of(st, x[q], y[q], z[q]);
     if (e >= N) continue;
-    b.key[e] = key[q];
+    if (rows_by_ranges(b)) b.key[e] = key[q];
     if (key[q] >= 0) atomicAdd(&cell[key[q]], 1);
     else if (e == st.start) cell[st.cell_off] = (int32_t)st.count;
   }
@@ -1748,17 +1785,21 @@ void launch_order_atoms(const BuildArgs& b, hipStream_t s) {
   // 42 : 40 for 6,912 (and its LDS holds a word per cell and per atom)
   if (b.N <= kOneAtoms && b.n_cells <= kOneAtoms) {
     hipLaunchKernelGGL(k_order_one_block, dim3(1), dim3(kOneThreads), 0, s, b);
-    hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
+    hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b, false);
     return;
   }
   hipLaunchKernelGGL(k_fill_cells, grid_for(std::max<int64_t>(b.n_cells, 8)), dim3(kBlock), 0, s, b);
   hipLaunchKernelGGL(k_cell_key, grid_for(b.N), dim3(kBlock), 0, s, b);
   hipLaunchKernelGGL(k_scan_1block, dim3(1), dim3(1024), 0, s, b.cell_count, b.cell_start, b.n_cells, g);
   hipLaunchKernelGGL(k_cell_scatter, grid_for(b.N), dim3(kBlock), 0, s, b);
-  if (b.cell_rows)
+  // cells as large as the cutoff asks for hold tens of atoms: a wave each
+  const bool ranked = b.cell_rows && (b.coarse || b.n_cells > kMaxBlocks);
+  if (ranked)
+    hipLaunchKernelGGL(k_cell_rank, grid_for(b.N), dim3(kBlock), 0, s, b);
+  else if (b.cell_rows)
     hipLaunchKernelGGL(k_cell_sort, dim3(div_up(b.n_cells, kBlock / 64)), dim3(kBlock), 0, s, b.cell_start,
                        b.cell_count, b.cell_fill, b.n_cells, b.ext_src, b.perm, g);
-  hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b);
+  hipLaunchKernelGGL(k_gather_atoms, grid_for(b.N), dim3(kBlock), 0, s, b, ranked);
   if (!b.rows) return;
   const int32_t Tn = b.per_type ? b.n_types : 1;
   const int32_t nb = (int32_t)type_row_blocks(b.N);

@@ -28,6 +28,7 @@ struct BuildArgs {
   int32_t wide_rows = 0;      // some structure has no cells: its rows come from k_build_rows_wide
   int32_t cell_rows = 0;      // some structure has cells: its rows come from k_build_rows_cells
   int32_t n_struct = 1;
+  bool coarse = false;        // larger cells than the cutoff asks for: one may hold every atom
   // optional: velocities and caller indices permuted with the positions
   const double* vel_src = nullptr;
   double* vel_dst = nullptr;

@@ -29,6 +29,7 @@ def _sorted(rows):
     (300, 60.0, (1, 1, 1)),       # cells of the cutoff, most of them empty
     (300, 3000.0, (1, 0, 1)),     # the whole cluster in a few cells
     (1700, 400.0, (1, 1, 1)),     # more cells than one block orders
+    (2600, 6000.0, (0, 0, 0)),    # over 1,024 atoms in a cell
 ])
 def test_rows_of_a_cluster_equal_the_oracle(n, side, pbc):
     pos = _cluster(n) + side / 2
@@ -41,7 +42,7 @@ def test_rows_of_a_cluster_equal_the_oracle(n, side, pbc):
     handle.close()
 
 
-@pytest.mark.parametrize("n,copies,side", [(150, 12, 500.0), (150, 120, 500.0)])
+@pytest.mark.parametrize("n,copies,side", [(150, 12, 500.0), (150, 120, 500.0), (9000, 2, 3000.0)])
 def test_copies_of_a_cluster_equal_the_one(n, copies, side):
     one = _cluster(n)
     p = synth.random_params(O.num_params(H), seed=1)
@@ -60,6 +61,23 @@ def test_copies_of_a_cluster_equal_the_one(n, copies, side):
     print(f"[vacuum] {copies} x {n}: |dU| {np.abs(U - ref['U']).max():.1e}", flush=True)
     assert np.abs(U - ref["U"]).max() <= 1e-5 and np.abs(F - ref["F"][:, None]).max() <= 1e-4
     handle.close()
+
+
+def test_crowded_cells_keep_their_order_during_a_run():
+    """A run whose every step sorts the atoms of crowded cells anew, and one that never
+    does after the first: two boxes, the same cluster."""
+    pos = _cluster(2600)
+    p = synth.solid_params(H, O.num_descriptors(H), O.num_params(H), seed=3)
+    vel = np.random.default_rng(5).normal(0, 2e-3, pos.shape)
+    out = []
+    for side, skin in ((80.0, 0.0), (6000.0, 0.0), (6000.0, 1e-3), (6000.0, 0.6)):
+        handle = nep.Handle(H, p, skin=skin)
+        out.append(handle.md_run(pos + side / 2, vel, np.zeros(2600, np.int32), [12.0], (side * np.eye(3)).reshape(9),
+                                 1.0, 6, 0, (0, 0, 0))[0] - side / 2)
+        print(f"[vacuum] {side} A, skin {skin}: {np.abs(out[-1] - out[0]).max():.1e}", flush=True)
+        handle.close()
+    # forces of the same rows differ by rounding: 2e-4 eV/A at mass 12 over 6 fs
+    assert max(np.abs(x - out[0]).max() for x in out) < 2e-4 * 9.65e-3 / 12 * 36 / 2
 
 
 def test_a_batch_of_sparse_and_dense_cells():
