@@ -1155,7 +1155,7 @@ __device__ __forceinline__ ImageOffset offset_at_build(const StructInfo& st, con
   return o;
 }
 
-template <bool BATCH, int G>
+template <bool BATCH, bool IMAGES, int G>
 __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict__ pos, int64_t N,
                                                         const int32_t* __restrict__ sid,
                                                         const StructInfo* __restrict__ structs,
@@ -1179,7 +1179,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
   uint16_t* __restrict__ lcd = L.cdR;
   const int nv = min(V.nnR[i], V.MR);
   const int steps = (nv + G - 1) / G;  // the same for the four lanes of an atom
-  const bool images = st.mode == kModeImages;
+  constexpr bool images = IMAGES;  // the structure's, one for all (a run's)
   const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
   int32_t na = 0, no = 0;
   // classes of the lane's first 64 candidates (t = local index) as bit masks;
@@ -1527,16 +1527,20 @@ void launch_check_rows(int64_t N, const int32_t* sid, const StructInfo* structs,
 // that it reads the partial forces through (131,072 atoms: 124 us against 43 + 58).
 bool rev_in_candidates(int64_t N, bool batch) { return !batch && N < kFewAtoms; }
 
+template <bool BATCH, int G>
+static void launch_filter_rows_g(const BuildArgs& b, const StructInfo& st0, const double* ref, const StructInfo* st_ref,
+                                 const Lists& V, const Lists& L, hipStream_t s) {
+  const auto kernel = st0.mode == kModeImages ? k_filter_rows<BATCH, true, G> : k_filter_rows<BATCH, false, G>;
+  hipLaunchKernelGGL(kernel, grid_for(b.N * G), dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs, st0, ref, st_ref, V,
+                     b.rcR2, b.rcA2, L, b.overflow);
+}
+
 template <int G>
 static void launch_filter_g(const BuildArgs& b, const StructInfo& st0, bool batch, const double* ref,
                             const StructInfo* st_ref, const Lists& V, const Lists& L, float4* disp, hipStream_t s) {
   const dim3 grid = grid_for(b.N * G);
-  if (batch)
-    hipLaunchKernelGGL((k_filter_rows<true, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
-                       st0, ref, st_ref, V, b.rcR2, b.rcA2, L, b.overflow);
-  else
-    hipLaunchKernelGGL((k_filter_rows<false, G>), grid, dim3(kBlock), 0, s, b.pos, b.N, b.sid, b.structs,
-                       st0, ref, st_ref, V, b.rcR2, b.rcA2, L, b.overflow);
+  batch ? launch_filter_rows_g<true, G>(b, st0, ref, st_ref, V, L, s)
+        : launch_filter_rows_g<false, G>(b, st0, ref, st_ref, V, L, s);
   if (batch)
     hipLaunchKernelGGL((k_reverse_from_candidates<true, G>), grid, dim3(kBlock), 0, s, b.N, V, L,
                        b.pos, b.types, b.sid, b.structs, disp, b.overflow + 2);

@@ -118,9 +118,9 @@ void launch_commit_rebuild(int64_t N, const double* pos2, const double* vel2, co
                            const StructInfo* st = nullptr, StructInfo* st_ref = nullptr);
 // Whether launch_filter_rows leaves the candidates' reverse positions in L.revR.
 bool rev_in_candidates(int64_t N, bool batch);
-// Exact rows L and the candidates' map from the candidate rows V.  ref: the
-// positions that V was built at; st_ref: the structure then (device; batch only,
-// else the structure is st0 throughout).
+// Exact rows L and the candidates' map from the candidate rows V of one structure,
+// st0 or, with `batch`, the device's present one (of st0's mode).  ref: the
+// positions that V was built at; st_ref: the structure then (device; batch only).
 void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, const double* ref,
                         const StructInfo* st_ref, const Lists& V, const Lists& L, float4* disp, hipStream_t s);
 // flag = 1 if an atom moved more than allowed since the last build, or will
