@@ -332,6 +332,7 @@ struct Branch {
   hipEvent_t done = nullptr;
   float *q = nullptr, *fp = nullptr, *U = nullptr, *sums = nullptr, *F = nullptr, *W = nullptr;
   float4* P = nullptr;
+  int64_t atoms = 0, entries = 0;  // what they hold: atoms, and row entries of them all
 };
 
 struct nep_handle {
@@ -374,6 +375,7 @@ struct nep_handle {
   hipStream_t md_stream = nullptr;  // capture/replay stream for null-stream callers
   Branch branch[kMaxBranches - 1];  // next to the handle's own stream and buffers
   hipEvent_t branch_fork = nullptr;
+  int64_t branch_refused = 0;       // atoms of a batch whose further branch found no memory (0: none yet)
   double* ens_state = nullptr;      // ensemble state, its chunk save, the saved cell and the last rebuild's
   double* ens_partial = nullptr;    // ensemble reduction partials
   int64_t ens_partial_cap = 0;
@@ -516,11 +518,15 @@ struct nep_handle {
     V = Lists{};
   }
 
+  void free_branch(Branch& b) {
+    dev_free(b.q); dev_free(b.fp); dev_free(b.U); dev_free(b.sums);
+    dev_free(b.F); dev_free(b.W); dev_free(b.P);
+    b.atoms = b.entries = 0;
+  }
+
   void free_branches() {
-    for (Branch& b : branch) {
-      dev_free(b.q); dev_free(b.fp); dev_free(b.U); dev_free(b.sums);
-      dev_free(b.F); dev_free(b.W); dev_free(b.P);
-    }
+    for (Branch& b : branch) free_branch(b);
+    branch_refused = 0;
   }
 
   void swap_buffers(Branch& b) {
@@ -529,7 +535,7 @@ struct nep_handle {
   }
 
   void free_lists() {
-    free_branches();  // sized like the rows and the atoms' buffers, which go with them
+    free_branches();  // their memory goes back with the rows'
     dev_free(L.nnR); dev_free(L.nlR); dev_free(L.cdR); dev_free(L.revR);
     dev_free(L.nnA);
     dev_free(P);
@@ -1186,22 +1192,23 @@ int compute_impl(nep_handle* h, int64_t N, const double* d_pos, const int32_t* d
 // own buffers.  Us per set of the 3-species training model, with 1, 2, 3 and 4
 // branches: 62, 50, 39, 37 for 244 atoms; 76, 58, 49, 47 for 6,532; 136, 103, 97,
 // 94 for 26,128; 219, 181, 175, 169 for 52,256; 472 and 407 for 130,640 with 1 and 2.
-// The buffers take about 3 KB per atom and branch: two beyond 65,536 atoms, where
-// more give little, and one beyond 262,144.
+// The buffers take about 3 KB per atom of the batch and branch: two beyond 65,536
+// atoms, where more give little, and one beyond 262,144.
 int population_branches(int64_t N, int32_t P) {
   const int most = N < 65536 ? 4 : (N < 262144 ? 2 : 1);
   return std::min<int>(P, most);
 }
 
-// The branches next to the handle's own, as many of n - 1 as are to be had.
-int ensure_branches(nep_handle* h, int n) {
+// The branches next to the handle's own for a batch of N atoms, as many of n - 1
+// as are to be had.  A branch that found no memory is not asked for again by
+// batches as large, so their graph is kept; new rows give it another chance.
+int ensure_branches(nep_handle* h, int64_t N, int n) {
   if (n < 2) return 1;
   if (!h->branch_fork && hipEventCreateWithFlags(&h->branch_fork, hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
     h->branch_fork = nullptr;
     return 1;
   }
-  const size_t c = (size_t)h->capN;
   const DevModel& M = h->M;
   for (int k = 0; k + 1 < n; ++k) {
     Branch& b = h->branch[k];
@@ -1210,15 +1217,20 @@ int ensure_branches(nep_handle* h, int n) {
       (void)hipGetLastError();
       return k + 1;
     }
-    if (b.P) continue;
+    if (N <= b.atoms && N * h->MR <= b.entries) continue;
+    if (h->branch_refused && N >= h->branch_refused) return k + 1;
+    const size_t c = (size_t)N;
     try {
+      h->free_branch(b);
       dev_alloc(b.q, c * M.NDp); dev_alloc(b.fp, c * M.NDp);
       dev_alloc(b.U, c); dev_alloc(b.sums, (size_t)sums_floats(M) * c);
       dev_alloc(b.F, 3 * c); dev_alloc(b.W, 9 * c);
       dev_alloc(b.P, (size_t)h->MR * c);
+      b.atoms = N;
+      b.entries = N * h->MR;
     } catch (const Failure&) {
-      dev_free(b.q); dev_free(b.fp); dev_free(b.U); dev_free(b.sums);
-      dev_free(b.F); dev_free(b.W); dev_free(b.P);
+      h->free_branch(b);
+      h->branch_refused = N;
       return k + 1;
     }
   }
@@ -1287,7 +1299,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     h->batch_cells = pp.n_cells;
   }
   pick_shape(h, pp);
-  const int branches = ensure_branches(h, population_branches(N, P));
+  const int branches = ensure_branches(h, N, population_branches(N, P));
   // everything the captured kernels hold by value or by address
   std::vector<unsigned char> key;
   auto put = [&](const void* p, size_t n) {
