@@ -789,7 +789,6 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     dev_alloc(h->pos_ext, 3 * c); dev_alloc(h->pos, 3 * c);
     dev_alloc(h->types_ext, c); dev_alloc(h->types, c); dev_alloc(h->sid_ext, c); dev_alloc(h->sid, c);
     dev_alloc(h->key, c); dev_alloc(h->cell, c); dev_alloc(h->perm, c); dev_alloc(h->inv, c);
-    dev_alloc(h->out_e, c); dev_alloc(h->out_f, 3 * c); dev_alloc(h->out_w, 9 * c);
     dev_alloc(h->q, (size_t)c * M.NDp); dev_alloc(h->fp, (size_t)c * M.NDp);
     dev_alloc(h->U, c); dev_alloc(h->sums, (size_t)sums_floats(M) * c);
     dev_alloc(h->F, 3 * c); dev_alloc(h->W, 9 * c);
@@ -818,6 +817,24 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     dev_alloc(h->vel_save, 3 * c); dev_alloc(h->types_save, c); dev_alloc(h->ext_save, c);
     dev_alloc(h->mass, kMaxTypes); dev_alloc(h->inv_mass, kMaxTypes);
   }
+}
+
+// Results of a call on host arrays too large for the staging, and the velocities of
+// a heat current (a call after ensure_atoms).
+void ensure_outputs(nep_handle* h) {
+  if (h->out_w) return;
+  const int64_t c = h->capN;
+  dev_alloc(h->out_e, c); dev_alloc(h->out_f, 3 * c); dev_alloc(h->out_w, 9 * c);
+}
+
+// Where the row builder parks members until the angular ones before them are
+// counted: the partial forces' rows, which are written after the rows are.
+Lists row_scratch(nep_handle* h) {
+  Lists V{};
+  V.MR = h->MR;
+  V.nlR = (int32_t*)h->P;
+  V.cdR = (uint16_t*)(V.nlR + (size_t)h->MR * h->capN);
+  return V;
 }
 
 struct Prepared {
@@ -918,9 +935,8 @@ Prepared prepare_batch(nep_handle* h, int32_t S, const int64_t* offs, const doub
   MR = std::max(MR, h->MR);
   MA = std::max(MA, h->MA);
   ensure_lists(h, N, MR, MA, pp.batch);
-  // candidate rows at r_list (= r_c^R, or r_c^R + skin)
-  const int32_t MV = r_list > h->hp.rc_radial ? estimate_capacity(r_list, max_density) : MR;
-  ensure_verlet(h, N, std::max(MV, h->V.MR));
+  // candidate rows at r_list = r_c^R + skin
+  if (r_list > h->hp.rc_radial) ensure_verlet(h, N, std::max(estimate_capacity(r_list, max_density), h->V.MR));
   if (S > h->cap_struct) {
     dev_alloc(h->structs, S);
     dev_alloc(h->offs, S + 1);
@@ -1001,12 +1017,11 @@ void build_rows_checked(nep_handle* h, const Prepared& pp, const BuildArgs& b, h
       const int32_t MR = std::max(h->MR, (int32_t)((fl[0] * 1.2 + 8) / 4 * 4 + 4));
       const int32_t MA = std::max(h->MA, (int32_t)((fl[1] * 1.2 + 8) / 4 * 4 + 4));
       ensure_lists(h, pp.N, MR, MA);
-      ensure_verlet(h, pp.N, std::max(h->V.MR, MR));
       launch_fill_i32(h->flags, 8, 0, s);
     }
     {
       Stage st(h, "neighbor_rows", s);
-      launch_build_rows(b, h->V, h->L, pp.batch ? h->disp : nullptr, s);
+      launch_build_rows(b, row_scratch(h), h->L, pp.batch ? h->disp : nullptr, s);
     }
     const int32_t* fl = (const int32_t*)(h->pinned + kPinFlags);
     HIPCHK(hipMemcpyAsync(h->pinned + kPinFlags, h->flags, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -1388,13 +1403,14 @@ struct ServerReq {
   uint64_t ticket = 0;
   int32_t kind = NEP_REQ_EVAL;
   int64_t n = 0;
+  int32_t MR = 0;           // slots of its rows
+  int32_t cells = 0;
   std::vector<double> pos, vel, mass;
   std::vector<int32_t> types;
   double box[9];
   int32_t pbc[3];
   int64_t n_steps = 0;
   double dt = 1.0;
-  size_t bytes = 0;
   double t_submit = 0, t_admit = 0, t_done = 0;
   int64_t steps_done = -1;  // -1: initial forces not yet evaluated
   int64_t off = 0;          // offset in the batch state while active
@@ -1484,16 +1500,56 @@ struct nep_server {
 
 namespace {
 
-// Bytes one request of n atoms needs on the device while active: its share of
-// the handle's workspace (rows at the density of its box, descriptor and
-// partial-force buffers) plus its state in the batch.
-size_t request_bytes(const nep_handle* h, int64_t n, double density) {
-  const double rc = h->hp.rc_radial, ra = h->hp.rc_angular;
-  const size_t MR = estimate_capacity(rc, density), MA = estimate_capacity(ra, density);
+// Slots of a radial row at this density.
+int32_t row_slots(const nep_handle* h, double density) {
+  return h->hp.max_nb_radial ? h->hp.max_nb_radial : estimate_capacity(h->hp.rc_radial, density);
+}
+
+// Bytes that `requests` requests of n atoms in all, in `cells` cells, need on the
+// device while active, in rows of MR slots: what ensure_atoms and ensure_lists allocate for a
+// batch without a skin, and the server's state and staging of an atom.
+size_t batch_bytes(const nep_handle* h, int64_t n, int64_t requests, int64_t cells, int32_t MR) {
   const DevModel& M = h->M;
-  const size_t per_atom = (MR + MA) * (4 + 2 + 4 + 12) + 8 + (size_t)M.NDp * 8 +
-                          (size_t)M.nA * M.NB * 4 + 48 + 40 + 64 + 24 * 2 + 24 + 8 + 72 + 16 + 8 + 1;
-  return per_atom * (size_t)n + 4096;
+  const size_t rows = (size_t)MR * (sizeof(int32_t) * 2 + sizeof(uint16_t) + 2 * sizeof(float4)) + 2 * 4;
+  const size_t atom = 2 * 24 + 8 * 4 + 2 * 4 * (size_t)M.NDp + 4 * (1 + (size_t)sums_floats(M) + 12) + 5;
+  const size_t state = 2 * (2 * 24 + 24 + 8 + 72 + 2 * 8 + 4 + 1);   // BatchState, twice for re-packing
+  const size_t staging = (8 * 8 + 4 + 19 * 8) * 3 / 2;                // uploads and results, with their headroom
+  return (rows + atom + state + staging) * (size_t)n + 3 * sizeof(int32_t) * (size_t)cells + 4096 * (size_t)requests;
+}
+
+// What the active requests (and `next`) ask for; the rows of a batch are as long as
+// its densest structure's.
+struct ActiveNeed {
+  int64_t n = 0, count = 0, cells = 0;
+  int32_t MR = 0;
+  ActiveNeed(const nep_server* sv, const ServerReq* next) {
+    for (const auto& r : sv->active) add(*r);
+    if (next) add(*next);
+  }
+  void add(const ServerReq& r) {
+    n += r.n;
+    cells += r.cells;
+    ++count;
+    MR = std::max(MR, r.MR);
+  }
+};
+
+// Bytes of the active requests, and of `next` with them, in rows as long as they
+// have been before.
+size_t active_bytes(const nep_server* sv, const ServerReq* next) {
+  const ActiveNeed a(sv, next);
+  return a.count ? batch_bytes(sv->h, a.n, a.count, a.cells, std::max(a.MR, sv->h->MR)) : 0;
+}
+
+// Before a tick that needs a larger workspace: longer rows for as many atoms as the
+// handle has had may be more than the budget, so the workspace starts anew then.
+void fit_workspace(nep_server* sv) {
+  nep_handle* h = sv->h;
+  const ActiveNeed a(sv, nullptr);
+  if ((a.n > h->capN || a.MR > h->MR) &&
+      batch_bytes(h, std::max(a.n, h->capN), a.count, std::max<int64_t>(a.cells, h->cap_cells),
+                  std::max(a.MR, h->MR)) > sv->budget)
+    h->free_workspace();
 }
 
 // One tick: every active request advances by one evaluation (and, for MD
@@ -1608,6 +1664,7 @@ void server_tick(nep_server* sv) {
     std::memcpy(&pbcs[3 * k], act[k]->pbc, sizeof act[k]->pbc);
   }
   launch_srv_kick_drift(N, b.pos, b.vel, b.F, b.hdm, b.dta, b.move, s);
+  fit_workspace(sv);
   Prepared pp = prepare_batch(h, S, offs.data(), boxes.data(), pbcs.data(), h->hp.rc_radial, false, true, s);
   order_and_build(h, pp, b.pos, b.types, s, [&] { forces(h, pp, s, nullptr, true, nullptr, false, true); });
   EvalArgs a = eval_args(h, pp, h->M);
@@ -1688,7 +1745,6 @@ void server_tick(nep_server* sv) {
   std::lock_guard<std::mutex> lk(sv->mu);
   for (auto& r : finished) {
     r->t_done = t;
-    sv->bytes_active -= r->bytes;
     sv->latencies.push_back(r->t_done - r->t_submit);
     sv->completed += 1;
     sv->t_last = t;
@@ -1696,6 +1752,7 @@ void server_tick(nep_server* sv) {
   }
   act.erase(std::remove_if(act.begin(), act.end(), [](const std::shared_ptr<ServerReq>& r) { return r->t_done > 0; }),
             act.end());
+  sv->bytes_active = active_bytes(sv, nullptr);
   // the remaining requests are re-packed next tick if their offsets moved
   sv->done_cv.notify_all();
 }
@@ -1708,10 +1765,12 @@ void server_loop(nep_server* sv) {
         std::unique_lock<std::mutex> lk(sv->mu);
         sv->cv.wait(lk, [&] { return sv->stop || !sv->queue.empty() || !sv->active.empty(); });
         if (sv->stop && sv->queue.empty() && sv->active.empty()) return;
-        // admission: free slots and HBM budget, first come first served
-        while (!sv->queue.empty() && (int32_t)sv->active.size() < sv->max_slots &&
-               sv->bytes_active + sv->queue.front()->bytes <= sv->budget) {
-          sv->bytes_active += sv->queue.front()->bytes;
+        // admission: free slots and HBM budget, first come first served (the first alone
+        // in any case: it fits by itself, if not in rows that others have made longer)
+        while (!sv->queue.empty() && (int32_t)sv->active.size() < sv->max_slots) {
+          const size_t with = active_bytes(sv, sv->queue.front().get());
+          if (with > sv->budget && !sv->active.empty()) break;
+          sv->bytes_active = with;
           sv->active.push_back(sv->queue.front());
           sv->queue.pop_front();
         }
@@ -1885,6 +1944,7 @@ int nep_compute(nep_handle* h, int64_t N, const double* pos, const int32_t* type
     }
     Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
     (void)pp;
+    if (energy || force || virial) ensure_outputs(h);
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     compute_impl(h, N, h->pos_ext, h->types_ext, box, pbc, energy ? h->out_e : nullptr,
@@ -1932,6 +1992,7 @@ int nep_heat_current(nep_handle* h, int64_t N, const double* pos, const double* 
     hipStream_t s = nullptr;
     Prepared pp = prepare(h, N, box, pbc, h->hp.rc_radial, false, s);
     (void)pp;
+    ensure_outputs(h);
     HIPCHK(hipMemcpyAsync(h->pos_ext, pos, 3 * N * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(h->types_ext, types, N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     // the velocities travel in the force buffer (3N doubles), unused by this call
@@ -2859,7 +2920,7 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       {
         Stage st(h, "neighbor_rows", s);
         BuildArgs b2 = build_args(h, pp, nullptr, nullptr, h->pos, h->types);
-        launch_build_rows(b2, h->V, h->L, nullptr, s);
+        launch_build_rows(b2, row_scratch(h), h->L, nullptr, s);
       }
       forces(h, pp, s, nullptr, thermo_every > 0 && step % thermo_every == 0);
       md.pos = h->pos;
@@ -2891,7 +2952,6 @@ static int md_impl(nep_handle* h, int64_t N, double* d_pos, double* d_vel, const
       const int32_t MR = std::max(h->MR, (int32_t)((fl[0] * 1.2 + 8) / 4 * 4 + 4));
       const int32_t MA = std::max(h->MA, (int32_t)((fl[1] * 1.2 + 8) / 4 * 4 + 4));
       ensure_lists(h, N, MR, MA);
-      ensure_verlet(h, N, std::max(h->V.MR, MR));
       HIPCHK(hipMemcpyAsync(h->pos, h->pos_save, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, s));
       HIPCHK(hipMemcpyAsync(h->vel, h->vel_save, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, s));
       HIPCHK(hipMemcpyAsync(h->types, h->types_save, N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
@@ -3107,8 +3167,9 @@ int nep_server_submit(nep_server* sv, const nep_request* rq, uint64_t* ticket) {
     }
     std::memcpy(r->box, rq->box, sizeof r->box);
     for (int k = 0; k < 3; ++k) r->pbc[k] = g.st.pbc[k];
-    r->bytes = request_bytes(h, n, (double)n / g.volume);
-    if (r->bytes > sv->budget) throw Failure{NEP_E_BUDGET, "request needs more device memory than the budget"};
+    r->MR = row_slots(h, (double)n / g.volume);
+    r->cells = g.n_cells;
+    if (batch_bytes(h, n, 1, r->cells, r->MR) > sv->budget) throw Failure{NEP_E_BUDGET, "request needs more device memory than the budget"};
     std::lock_guard<std::mutex> lk(sv->mu);
     if (!sv->fatal.empty()) throw Failure{NEP_E_HIP, "server stopped: " + sv->fatal};
     r->ticket = sv->next_ticket++;
