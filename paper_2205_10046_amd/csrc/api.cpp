@@ -201,6 +201,16 @@ void dev_free(T*& p) {
   p = nullptr;
 }
 
+// A buffer of `need` elements where it has fewer.  The capacity is 0 while there is
+// none: a call that found no memory leaves nothing that a smaller one would use.
+template <class T, class Cap>
+void dev_grow(T*& p, Cap& cap, Cap need) {
+  if (need <= cap) return;
+  cap = 0;
+  dev_alloc(p, (size_t)need);
+  cap = need;
+}
+
 struct Geometry {
   StructInfo st;
   int32_t n_cells;
@@ -746,11 +756,16 @@ void ensure_lists(nep_handle* h, int64_t N, int32_t MR, int32_t MA, bool batch =
     throw Failure{NEP_E_NEIGHBOR_OVERFLOW, "neighbour rows longer than 65535 entries"};
   h->free_lists();
   const int64_t cap = std::max(N, h->capN);
-  dev_alloc(h->L.nnR, cap); dev_alloc(h->L.nnA, cap);
-  dev_alloc(h->L.nlR, (size_t)MR * cap); dev_alloc(h->L.cdR, (size_t)MR * cap);
-  dev_alloc(h->L.revR, (size_t)MR * cap);
-  dev_alloc(h->P, (size_t)MR * cap);
-  if (batch) dev_alloc(h->disp, (size_t)MR * cap);
+  try {
+    dev_alloc(h->P, (size_t)MR * cap);
+    if (batch) dev_alloc(h->disp, (size_t)MR * cap);
+    dev_alloc(h->L.nnR, cap); dev_alloc(h->L.nnA, cap);
+    dev_alloc(h->L.nlR, (size_t)MR * cap); dev_alloc(h->L.cdR, (size_t)MR * cap);
+    dev_alloc(h->L.revR, (size_t)MR * cap);
+  } catch (const Failure&) {
+    h->free_workspace();  // a smaller call starts anew, not with as many atoms or as long rows
+    throw;
+  }
   h->MR = MR;
   h->MA = MA;
   h->L.MR = MR;
@@ -765,6 +780,10 @@ void ensure_verlet(nep_handle* h, int64_t N, int32_t MV) {
   if (MV > kMaxRow) throw Failure{NEP_E_NEIGHBOR_OVERFLOW, "candidate rows longer than 65535 entries"};
   h->free_verlet();
   const int64_t cap = h->capN;
+  if (!h->ref_save) {
+    dev_alloc(h->pos_ref, 3 * cap);
+    dev_alloc(h->ref_save, 3 * cap);
+  }
   dev_alloc(h->V.nnR, cap);
   dev_alloc(h->V.nnA, cap);
   dev_alloc(h->V.nlR, (size_t)MV * cap);
@@ -773,10 +792,6 @@ void ensure_verlet(nep_handle* h, int64_t N, int32_t MV) {
   dev_alloc(h->V.fmap, (size_t)MV * cap);
   h->V.MR = MV;
   h->V.MA = 0;
-  if (!h->pos_ref) {
-    dev_alloc(h->pos_ref, 3 * cap);
-    dev_alloc(h->ref_save, 3 * cap);
-  }
 }
 
 // Per-atom buffers sized for N atoms (contents are not preserved).
@@ -805,17 +820,19 @@ void ensure_atoms(nep_handle* h, int64_t N, int32_t n_cells, bool md) {
     h->MA = MA;
   }
   if (n_cells > h->cap_cells) {
+    h->cap_cells = 0;
     dev_alloc(h->cell_count, n_cells); dev_alloc(h->cell_fill, n_cells);
     dev_alloc(h->cell_start, n_cells);
     h->cap_cells = n_cells;
   }
   if (md && !h->vel) {
     const int64_t c = h->capN;
-    dev_alloc(h->pos2, 3 * c); dev_alloc(h->vel, 3 * c); dev_alloc(h->vel2, 3 * c);
+    dev_alloc(h->pos2, 3 * c); dev_alloc(h->vel2, 3 * c);
     dev_alloc(h->vel_ext, 3 * c); dev_alloc(h->types2, c); dev_alloc(h->ext_id, c);
     dev_alloc(h->ext_id2, c); dev_alloc(h->F_save, 3 * c); dev_alloc(h->pos_save, 3 * c);
     dev_alloc(h->vel_save, 3 * c); dev_alloc(h->types_save, c); dev_alloc(h->ext_save, c);
     dev_alloc(h->mass, kMaxTypes); dev_alloc(h->inv_mass, kMaxTypes);
+    dev_alloc(h->vel, 3 * c);  // last: with it the others are there
   }
 }
 
@@ -938,6 +955,7 @@ Prepared prepare_batch(nep_handle* h, int32_t S, const int64_t* offs, const doub
   // candidate rows at r_list = r_c^R + skin
   if (r_list > h->hp.rc_radial) ensure_verlet(h, N, std::max(estimate_capacity(r_list, max_density), h->V.MR));
   if (S > h->cap_struct) {
+    h->cap_struct = 0;
     dev_alloc(h->structs, S);
     dev_alloc(h->offs, S + 1);
     h->cap_struct = S;
@@ -1297,8 +1315,7 @@ int batch_impl(nep_handle* h, int32_t S, const int64_t* offs, const double* d_po
     const int64_t need = (int64_t)P * TL.set_bytes;
     if (need > h->pop_tables_cap) {
       HIPCHK(hipStreamSynchronize(s));
-      dev_alloc(h->pop_tables, (size_t)need);
-      h->pop_tables_cap = need;
+      dev_grow(h->pop_tables, h->pop_tables_cap, need);
     }
     for (int32_t p = 0; p < P; ++p) models.push_back(model_at(h->M, TL, h->pop_tables + p * TL.set_bytes));
   } else {
@@ -1835,8 +1852,7 @@ void heat_current_impl(nep_handle* h, int64_t N, const double* d_pos, const doub
   const int64_t n_part = (N + 255) / 256;
   if (3 * n_part > h->heat_part_cap) {
     HIPCHK(hipStreamSynchronize(s));
-    dev_alloc(h->heat_part, (size_t)(3 * n_part));
-    h->heat_part_cap = 3 * n_part;
+    dev_grow(h->heat_part, h->heat_part_cap, 3 * n_part);
   }
   Stage st(h, "heat_current", s);
   launch_heat_current(h->W, N, h->perm, d_vel, d_heat, d_total, h->heat_part, n_part, s);
@@ -2064,14 +2080,12 @@ int nep_batch_loss(nep_handle* h, int32_t n_struct, const int64_t* offsets, int3
     const int64_t need_part = (int64_t)n_param_sets * loss_chunks(N) * 6;  // six sums per chunk
     if (need_part > h->loss_part_cap) {
       HIPCHK(hipStreamSynchronize(s));
-      dev_alloc(h->loss_part, (size_t)need_part);
-      h->loss_part_cap = need_part;
+      dev_grow(h->loss_part, h->loss_part_cap, need_part);
     }
     if (n_struct + 1 > h->loss_offs_cap) {
       HIPCHK(hipStreamSynchronize(s));
-      dev_alloc(h->loss_offs, (size_t)n_struct + 1);
-      h->loss_offs_cap = n_struct + 1;
       h->loss_offs_host.clear();
+      dev_grow(h->loss_offs, h->loss_offs_cap, (int64_t)n_struct + 1);
     }
     // the offsets are uploaded only when they differ from the last call's
     if (h->loss_offs_host.size() != (size_t)n_struct + 1 ||
@@ -2459,10 +2473,7 @@ int md_skin(nep_handle* h, const Prepared& pp, double* d_pos, double* d_vel, con
     if (!h->ens_state) dev_alloc(h->ens_state, 4 * 512 / sizeof(double));
     static_assert(sizeof(StructInfo) <= 512, "staging slot");
     const int64_t need = std::max<int64_t>(ens_partials(N), div_up(N, 256) + 1) + 1;
-    if (need > h->ens_partial_cap) {
-      dev_alloc(h->ens_partial, (size_t)need);
-      h->ens_partial_cap = need;
-    }
+    dev_grow(h->ens_partial, h->ens_partial_cap, need);
     est = (EnsState*)h->ens_state;
     EnsState init{};
     init.heat = ens_state[1];
