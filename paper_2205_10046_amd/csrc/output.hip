@@ -175,17 +175,18 @@ __global__ void k_descriptors_out(const float* __restrict__ q, int64_t N, int ND
                                   const int32_t* __restrict__ perm, double* __restrict__ out) {
   // a thread to a value: both sides in runs of ND (a thread to an atom: 16.7 us for the 6,912
   // atoms of the 4-species alloy, this 3.9)
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t k = x / ND;
-  if (k >= N) return;
-  const int d = (int)(x - k * ND);
-  out[perm[k] * (int64_t)ND + d] = (double)q[k * NDp + d];
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N * ND; x += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = x / ND;
+    const int d = (int)(x - k * ND);
+    out[perm[k] * (int64_t)ND + d] = (double)q[k * NDp + d];
+  }
 }
 
 void launch_descriptors_out(const float* q, int64_t N, int NDp, int ND, const int32_t* perm,
                             double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_descriptors_out, dim3(div_up(N * ND, kBlock)), dim3(kBlock), 0, s, q, N, NDp,
-                     ND, perm, out);
+  // at most 2^31 threads (a grid takes fewer than 2^32): more values are further turns
+  const int64_t blocks = std::min<int64_t>((N * ND + kBlock - 1) / kBlock, 1 << 23);
+  hipLaunchKernelGGL(k_descriptors_out, dim3((unsigned)blocks), dim3(kBlock), 0, s, q, N, NDp, ND, perm, out);
 }
 
 __global__ void k_inverse_perm(const int32_t* __restrict__ perm, int64_t N,
