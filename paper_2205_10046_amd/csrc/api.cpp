@@ -1093,8 +1093,12 @@ void order_and_build(nep_handle* h, const Prepared& pp, const double* pos_src, c
 // against four: the 4-species alloy 54 : 32 at 4,000 atoms, 56 : 49 at 10,976,
 // 80 : 82 at 23,328; l_max = 6 62 : 45 at 8,192 and 98 : 119 at 27,648; a batch's
 // whole pass 111 : 95 at 6,532 atoms and 117 : 130 at 13,064.  A batch keeps the
-// shape of the handle's first batch, so that a structure's result does not
-// depend on the others in it.
+// shape of the handle's first batch (so does a run with a changing cell, which
+// uses the batched kernels), so that a structure's result does not depend, to
+// the last bit, on the others in its batch.  It does on that first batch, and a
+// first batch on the other side of the line costs a later one a tenth: the
+// training cells take 1,249 us for 132,820 atoms and 2,752 for 332,050 after a
+// small first batch, 1,128 and 2,419 after a large one.
 constexpr int64_t kQuadAtoms = 16384;
 
 const Tuning& pick_shape(nep_handle* h, const Prepared& pp) {

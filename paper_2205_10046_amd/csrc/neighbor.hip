@@ -3,23 +3,25 @@
 // The paper assumes neighbour counts NN_i and rows NL_im are given and uses
 // the minimum image; it does not say how they are built.  Here:
 //   1. atoms are binned into cells at least r_c wide along every cell vector
-//      (fractional coordinates, float64), one cell per small structure;
+//      (fractional coordinates, float64; wider in a box that is mostly empty),
+//      one cell per small structure;
 //   2. a deterministic counting sort gives the internal atom order
 //      (structure, cell, caller index): the atoms of a cell are contiguous;
-//   3. one thread per atom scans the stencil cells in increasing cell index,
-//      so candidate j arrive in increasing internal index and every candidate
-//      row (radius r_c^R, or r_c^R + skin in MD with a skin) comes out sorted
-//      by (j, image) without a sort;
+//   3. the lanes of an atom walk the stencil cells in increasing cell index, or
+//      the atoms and images of a small structure in order, and place members by
+//      counts over the lanes, so every row comes out sorted by (j, image)
+//      without a sort;
 //   4. membership is the strict float64 test |d|^2 < r_c^2 on the canonical
 //      displacement (no fused multiply-add), the same test for both cutoffs;
-//   5. the exact radial row is filtered from the candidates with the
-//      angular-range entries (|d|^2 < (r_c^A)^2) first and the rest after,
-//      each part in candidate order: the angular row of the sums is the
-//      first nnA entries of the radial row;
-//   6. rev[m][i] locates i in the radial row of its m-th neighbour: a binary
-//      search on the sorted candidate rows (once per candidate build) and the
-//      candidate -> exact position map of every filter, so the force pass
-//      can gather dU_j/dr_ji without atomics.
+//   5. an exact radial row has the angular-range entries (|d|^2 < (r_c^A)^2)
+//      first and the rest after, each part in order: the angular row of the sums
+//      is the first nnA entries of the radial row.  A call without a skin builds
+//      it at once; a run with a skin filters it at every step from candidate
+//      rows (radius r_c^R + skin);
+//   6. rev[m][i] locates i in the radial row of its m-th neighbour, so the force
+//      pass can gather dU_j/dr_ji without atomics: a binary search on the sorted
+//      parts of exact rows, or one on the candidate rows (once per candidate
+//      build) and the candidate -> exact position map of every filter.
 #include <algorithm>
 
 #include "nep_kernels.h"
@@ -42,11 +44,6 @@ __device__ __forceinline__ bool gated_off(const int32_t* gate) { return gate && 
 __global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = v;
-}
-
-__global__ void k_fill_i32_gated(int32_t* a, int64_t n, int32_t v, const int32_t* gate) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !gated_off(gate)) a[i] = v;
 }
 
 // Structure id of every caller-order atom from the offsets array.
@@ -1178,7 +1175,7 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
   int32_t* __restrict__ lrev = L.revR;
   uint16_t* __restrict__ lcd = L.cdR;
   const int nv = min(V.nnR[i], V.MR);
-  const int steps = (nv + G - 1) / G;  // the same for the four lanes of an atom
+  const int steps = (nv + G - 1) / G;  // the same for every lane of an atom
   constexpr bool images = IMAGES;  // the structure's, one for all (a run's)
   const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
   int32_t na = 0, no = 0;
@@ -1343,7 +1340,8 @@ __global__ void __launch_bounds__(kBlock) k_filter_rows(const double* __restrict
 // rev of the exact rows: the filter left in L.revR[p][i] the candidate
 // position of i in the row of j = L.nlR[p][i]; the exact position there is
 // V.fmap of that candidate entry, written in place.  G lanes per atom
-// take exact entries p = s, s + G, ..., four or sixteen as in the filter; a lane loads the words of kFilterChunk entries, then their map
+// take exact entries p = s, s + G, ..., four or sixteen as in the filter; a lane
+// loads the words of kFilterChunk entries, then their map
 // entries, then writes them.  For a batch (DISP) it also writes every
 // entry's float32 displacement and species (as bits), read by each parameter
 // set's passes.
@@ -1590,23 +1588,6 @@ void launch_check_displacement(const double* pos, const double* ref, const doubl
                                const double* mu_cum, double rc, double rl) {
   hipLaunchKernelGGL(k_check_displacement, grid_for(N), dim3(kBlock), 0, s, pos, ref, vel, N, thr2, horizon,
                      flag, mu_cum, rc, rl);
-}
-
-template <class T>
-__global__ void k_copy_gated(T* __restrict__ dst, const T* __restrict__ src, int64_t n,
-                             const int32_t* gate) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !gated_off(gate)) dst[i] = src[i];
-}
-
-void launch_copy_gated_f64(double* dst, const double* src, int64_t n, const int32_t* gate,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_copy_gated<double>, grid_for(n), dim3(kBlock), 0, s, dst, src, n, gate);
-}
-
-void launch_copy_gated_i32(int32_t* dst, const int32_t* src, int64_t n, const int32_t* gate,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_copy_gated<int32_t>, grid_for(n), dim3(kBlock), 0, s, dst, src, n, gate);
 }
 
 int64_t type_row_blocks(int64_t N) { return div_up(N, kBlock); }

@@ -14,8 +14,9 @@
 //                                     reverse index and candidate -> exact map
 //   q, fp    float32 [N][ND_pad]      descriptor / dU/dq rows (network input)
 //   sums     float32x4 [NT*NBT][N][4] angular sums S_{n,k} in tiles of 4 x 4 (pair.h)
-//   P        float32x4 [MR][N]        dU_i/dr_ij per radial entry, radial and
-//                                     angular parts summed (w unused)
+//   P        float32x4 [N][MR]        dU_i/dr_ij per radial entry, radial and
+//                                     angular parts summed (w unused); while the
+//                                     rows of a call without a skin are built, scratch
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -117,26 +118,6 @@ __device__ inline double norm2_exact(double dx, double dy, double dz) {
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-// Displacement of list entry (i -> j, code) from internal positions.
-__device__ inline void entry_disp(const double* __restrict__ pos, int64_t N, int64_t i,
-                                  int64_t j, const StructInfo& st, uint16_t code,
-                                  double& dx, double& dy, double& dz) {
-#pragma clang fp contract(off)
-  double Dx = pos[j] - pos[i];
-  double Dy = pos[N + j] - pos[N + i];
-  double Dz = pos[2 * N + j] - pos[2 * N + i];
-  int n0, n1, n2;
-  min_image(st, Dx, Dy, Dz, n0, n1, n2);
-  if (code != kCodeCenter) {
-    int a, b, c;
-    split_code(code, a, b, c);
-    n0 += a;
-    n1 += b;
-    n2 += c;
-  }
-  image_disp(st, Dx, Dy, Dz, n0, n1, n2, dx, dy, dz);
-}
-
 __host__ __device__ constexpr int round4(int n) { return (n + 3) / 4 * 4; }
 // Smallest stride >= n floats that is 4 mod 64 (bank-spread species pairs).
 __host__ __device__ constexpr int pair_stride(int n) { return n + ((4 - n % 64) + 64) % 64; }
@@ -171,8 +152,7 @@ struct DevModel {
   float C5[3];
 };
 
-// Internal neighbour lists of one build.  Row capacities stay below 65535
-// so positions inside a row fit the uint16 maps.
+// Internal neighbour lists of one build; row capacities stay below kMaxRow.
 struct Lists {
   int32_t MR, MA;           // row capacities
   int32_t* nnR;
@@ -180,8 +160,6 @@ struct Lists {
   uint16_t* cdR;
   int32_t* revR;
   int32_t* nnA;
-  int32_t* nlA;
-  uint16_t* cdA;
   int32_t* fmap;            // candidate rows only: candidate -> exact position, or -1
 };
 

@@ -130,10 +130,6 @@ void launch_filter_rows(const BuildArgs& b, const StructInfo& st0, bool batch, c
 void launch_check_displacement(const double* pos, const double* ref, const double* vel, int64_t N,
                                double thr2, double horizon, int32_t* flag, hipStream_t s,
                                const double* mu_cum, double rc, double rl);
-void launch_copy_gated_f64(double* dst, const double* src, int64_t n, const int32_t* gate,
-                           hipStream_t s);
-void launch_copy_gated_i32(int32_t* dst, const int32_t* src, int64_t n, const int32_t* gate,
-                           hipStream_t s);
 int64_t type_row_blocks(int64_t N);
 
 // descriptor.hip / force.hip: return false if no kernel exists for the model
@@ -236,10 +232,6 @@ void launch_srv_place(const int64_t* tab, int32_t n_req, int64_t max_n, const Sr
 void launch_srv_collect(const int64_t* tab, int32_t n_req, int64_t max_n, int64_t ld, const double* E,
                         const double* F, const double* W, const double* pos, const double* vel, double* out,
                         hipStream_t s);
-void launch_gather3_gated(const int32_t* src, int64_t N, const double* in, double* out,
-                          const int32_t* gate, hipStream_t s);
-void launch_gather_i32_gated(const int32_t* src, int64_t N, const int32_t* in, int32_t* out,
-                             const int32_t* gate, hipStream_t s);
 void launch_gather_i32(const int32_t* src, int64_t N, const int32_t* in, int32_t* out, hipStream_t s);
 
 // ensemble.hip: thermostats and barostats (kinds as NEP_ENS_* in nep.h)
